@@ -44,8 +44,9 @@ def flags():
     return CODEGEN_FLAGS + ["-I", INCLUDE, "-I", CSRC, "-Wall", "-Wno-unused-function"]
 
 
-# generated code a source includes besides internal.h
-INCLUDES = {"attn_bf16.hip": ["attn_d128_loop.inc", "attn_d64_loop.inc"]}
+# what a source includes besides internal.h: shared and generated code
+INCLUDES = {"attn_bf16.hip": ["attn_tile.h", "attn_d128_loop.inc", "attn_d64_loop.inc"],
+            "attn_f32.hip": ["attn_tile.h"]}
 
 
 def source_id(name: str) -> str:

@@ -69,32 +69,13 @@
 //   row i = 8*(r/4) + 4*(l/32) + (r%4), column j = l % 32.
 #include <type_traits>
 
+#include "attn_tile.h"
 #include "internal.h"
-
-
 
 namespace ditango {
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x8 __attribute__((ext_vector_type(8)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-
-#define LDS_PTR(T, p) ((__attribute__((address_space(3))) T*)(p))
 #define GLOBAL_PTR(T, p) ((const __attribute__((address_space(1))) T*)(p))
-
-constexpr float kLn2 = 0.6931471805599453f;
-
-__device__ __forceinline__ f32x16 mfma32(const bf16x8& a, const bf16x8& b, const f32x16& c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-}
-
-__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // LDS byte address of a pointer into the workgroup's shared memory
 __device__ __forceinline__ uint32_t lds_addr(const void* p) {
@@ -117,16 +98,6 @@ __device__ __forceinline__ void lds_dma16(const void* base, uint32_t voff, uint3
                :
                : "v"(voff), "s"(sbase), "s"(m0v)
                : "memory", "m0");
-}
-
-// max / sum of x over lanes l and l^32 (the two lanes holding one query row)
-__device__ __forceinline__ float pair_max(float x) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-__device__ __forceinline__ float pair_sum(float x) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
 // f(std::integral_constant<int, I>{}) for I = 0 .. N-1, unrolled
@@ -166,15 +137,6 @@ struct Cfg {
   static_assert(LOADS % NW == 0, "tile loads must split evenly over waves");
   static_assert(BN % 32 == 0, "key tile");
 };
-
-// unit swizzles (see the file comment): 16 consecutive keys reading the same
-// unit, and 4 consecutive keys x 4 consecutive units, are bank-group distinct
-template <int D> __device__ __forceinline__ int swz_k(int key) {
-  return D == 128 ? (key & 15) : ((key >> 1) & 7);
-}
-template <int D> __device__ __forceinline__ int swz_v(int key) {
-  return D == 128 ? ((key & 3) << 2) : (((key >> 1) & 1) << 2);
-}
 
 // s_waitcnt immediate that waits until at most n vector-memory operations of
 // this wave are outstanding (expcnt and lgkmcnt not waited for)
