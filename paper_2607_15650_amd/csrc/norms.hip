@@ -4,10 +4,10 @@
 // These feed the error model of the selection planner: the scale ratio
 // alpha(i) = ||AS(i)|| / ||AS(i_loc)|| (Sec. 4.1.2, Eq. scale_ratio) and the
 // local-state drift ||AS_t(i_loc) - AS_tc(i_loc)|| that the age penalty
-// extrapolates (Eq. error_extrapolation).  Bound by HBM: every listed slot
-// (and REF once per slot) is read once.  The sums of squares are reduced in a
-// fixed order (per-workgroup tree, then one workgroup over the partials), so
-// the result is bitwise reproducible.
+// extrapolates (Eq. error_extrapolation).  Bound by HBM: every listed slot is
+// read once (and REF once per four slots).  The sums of squares are reduced in
+// a fixed order (per workgroup, then one workgroup per slot over the
+// partials), so the result is bitwise reproducible.
 #include "internal.h"
 
 namespace ditango {
@@ -17,114 +17,137 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x8 __attribute__((ext_vector_type(8)));
 
-// 8 consecutive elements, loaded in the state type and used as float
-template <typename T> struct Raw8;
-template <> struct Raw8<__bf16> {
+// 16 bytes of a state (8 bf16 or 4 float32 elements), loaded in the state
+// type and squared as float
+template <typename T> struct Unit;
+template <> struct Unit<__bf16> {
   typedef bf16x8 type;
-  static __device__ __forceinline__ type load(const __bf16* p) { return __builtin_nontemporal_load((const bf16x8*)p); }
-  static __device__ __forceinline__ f32x8 f32(const type& x) { return __builtin_convertvector(x, f32x8); }
+  typedef f32x8 wide;
+  static constexpr int N = 8;
 };
-template <> struct Raw8<float> {
-  typedef f32x8 type;
-  static __device__ __forceinline__ type load(const float* p) {
-    const f32x4 a = __builtin_nontemporal_load((const f32x4*)p);
-    const f32x4 b = __builtin_nontemporal_load((const f32x4*)(p + 4));
-    return f32x8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-  }
-  static __device__ __forceinline__ f32x8 f32(const type& x) { return x; }
+template <> struct Unit<float> {
+  typedef f32x4 type;
+  typedef f32x4 wide;
+  static constexpr int N = 4;
 };
 
-
-// grid: (blocks per slot, n_slots).  Each workgroup sums the squares of a fixed
-// range of 8-element chunks of one slot into partial[slot][block].
-template <typename T>
-__global__ __launch_bounds__(kNormThreads) void norms_partial_kernel(const NormArgs a) {
-  __shared__ float red[kNormThreads];
-  const int tid = threadIdx.x;
-  const int si = blockIdx.y;
-  const T* __restrict__ src = (const T*)a.states + (int64_t)a.slots[si] * a.elems;
-  const T* __restrict__ ref = (const T*)a.ref;
-  const int64_t chunks = a.elems / 8;
-  const int64_t c0 = (int64_t)blockIdx.x * kNormChunksPerBlock;
-  // batches of kBatch chunks: every load of a batch (state and reference)
-  // is issued before the first is used, and unconditionally (a chunk past
-  // the end reads the last chunk and is then replaced by zeros, which leave
-  // the sum's bits alone): a load under a per-lane condition is waited for
-  // inside its branch.  Chunks stay in the state type until they are used.
-  constexpr int kPer = kNormChunksPerBlock / kNormThreads;
-  constexpr int kBatch = 8;
-  static_assert(kPer % kBatch == 0, "batches");
-  using R = Raw8<T>;
-  float sum = 0.f;
-#pragma unroll 1
-  for (int i0 = 0; i0 < kPer; i0 += kBatch) {
-    typename R::type x[kBatch], y[kBatch];
+// the workgroup's sum of x in every thread, in a fixed order: a butterfly
+// over the wave, then the waves in order
+__device__ __forceinline__ float block_sum(float x, float* red) {
 #pragma unroll
-    for (int i = 0; i < kBatch; ++i) {
-      const int64_t c = c0 + (int64_t)(i0 + i) * kNormThreads + tid;
-      x[i] = R::load(src + (c < chunks ? c : chunks - 1) * 8);
-    }
-    if (ref != nullptr) {
-#pragma unroll
-      for (int i = 0; i < kBatch; ++i) {
-        const int64_t c = c0 + (int64_t)(i0 + i) * kNormThreads + tid;
-        y[i] = R::load(ref + (c < chunks ? c : chunks - 1) * 8);
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < kBatch; ++i) {
-      const bool ok = c0 + (int64_t)(i0 + i) * kNormThreads + tid < chunks;
-      f32x8 v = R::f32(x[i]);
-      if (ref != nullptr) v -= R::f32(y[i]);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float d = ok ? v[e] : 0.f;
-        sum = __builtin_fmaf(d, d, sum);
-      }
-    }
-  }
-  red[tid] = sum;
+  for (int k = 32; k > 0; k >>= 1) x += __shfl_xor(x, k, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
   __syncthreads();
+  float sum = 0.f;
 #pragma unroll
-  for (int off = kNormThreads / 2; off > 0; off >>= 1) {
-    if (tid < off) red[tid] += red[tid + off];
-    __syncthreads();
-  }
-  if (tid == 0) a.partial[(int64_t)si * a.blocks + blockIdx.x] = red[0];
+  for (int w = 0; w < kNormThreads / 64; ++w) sum += red[w];
+  return sum;
 }
 
-__global__ __launch_bounds__(kNormThreads) void norms_final_kernel(const NormArgs a) {
-  __shared__ float red[kNormThreads];
+// Each workgroup sums the squares of a fixed range of elements of NS listed
+// slots (NS = 1, or up to 4 that share the reference) into
+// partial[slot][block].  grid: (blocks per slot, groups of NS slots).
+//
+// Bound by HBM.  The slots of a call that subtracts a reference are read
+// together, so that the reference is read once and not once per slot: four
+// snapshots of 9,450 rows x 40 heads at D=128 in bf16 125.8 -> 77.1 us (484 MB
+// instead of 774, 6.3 TB/s; the final sums included, one workgroup per slot
+// instead of one for all); without a reference 8 slots 136 -> 119 us, 3
+// float32 slots 104 -> 88 us (consecutive 16-byte loads).
+template <typename T, int NS, bool REF>
+__global__ __launch_bounds__(kNormThreads) void norms_partial_kernel(const NormArgs a, int slot0) {
+  __shared__ float red[NS][kNormThreads / 64];
+  using U = Unit<T>;
   const int tid = threadIdx.x;
-  for (int si = 0; si < a.n; ++si) {
-    float sum = 0.f;
-    for (int b = tid; b < a.blocks; b += kNormThreads) sum += a.partial[(int64_t)si * a.blocks + b];
-    red[tid] = sum;
-    __syncthreads();
+  const int s0 = slot0 + blockIdx.y * NS;
+  const int64_t units = a.elems / U::N;
+  constexpr int kPer = kNormChunksPerBlock * 8 / U::N / kNormThreads;   // units per thread and slot
+  const int64_t u0 = (int64_t)blockIdx.x * kPer * kNormThreads + tid;
+  const T* src[NS];
 #pragma unroll
-    for (int off = kNormThreads / 2; off > 0; off >>= 1) {
-      if (tid < off) red[tid] += red[tid + off];
-      __syncthreads();
+  for (int j = 0; j < NS; ++j) src[j] = (const T*)a.states + (int64_t)a.slots[s0 + j] * a.elems;
+  const T* ref = (const T*)a.ref;
+  // batches of units: every load of a batch (states and reference) is issued
+  // before the first is used, and unconditionally (a unit past the end reads
+  // the last unit and is then replaced by zeros, which leave the sum's bits
+  // alone): a load under a per-lane condition is waited for inside its branch.
+  constexpr int kBatch = NS == 1 ? 8 : 4;
+  static_assert(kPer % kBatch == 0, "batches");
+  float sum[NS];
+#pragma unroll
+  for (int j = 0; j < NS; ++j) sum[j] = 0.f;
+#pragma unroll 1
+  for (int i0 = 0; i0 < kPer; i0 += kBatch) {
+    typename U::type x[NS][kBatch], y[kBatch];
+#pragma unroll
+    for (int i = 0; i < kBatch; ++i) {
+      const int64_t u = u0 + (int64_t)(i0 + i) * kNormThreads;
+      const int64_t at = (u < units ? u : units - 1) * U::N;
+      if constexpr (REF) y[i] = __builtin_nontemporal_load((const typename U::type*)(ref + at));
+#pragma unroll
+      for (int j = 0; j < NS; ++j) x[j][i] = __builtin_nontemporal_load((const typename U::type*)(src[j] + at));
     }
-    if (tid == 0) a.norms[si] = __builtin_sqrtf(red[0]);
-    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kBatch; ++i) {
+      const bool ok = u0 + (int64_t)(i0 + i) * kNormThreads < units;
+#pragma unroll
+      for (int j = 0; j < NS; ++j) {
+        typename U::wide v = __builtin_convertvector(x[j][i], typename U::wide);
+        if constexpr (REF) v -= __builtin_convertvector(y[i], typename U::wide);
+#pragma unroll
+        for (int e = 0; e < U::N; ++e) {
+          const float d = ok ? v[e] : 0.f;
+          sum[j] = __builtin_fmaf(d, d, sum[j]);
+        }
+      }
+    }
   }
+#pragma unroll
+  for (int j = 0; j < NS; ++j) {
+    const float t = block_sum(sum[j], red[j]);
+    if (tid == 0) a.partial[(int64_t)(s0 + j) * a.blocks + blockIdx.x] = t;
+  }
+}
+
+// one workgroup per listed slot
+__global__ __launch_bounds__(kNormThreads) void norms_final_kernel(const NormArgs a) {
+  __shared__ float red[kNormThreads / 64];
+  const int si = blockIdx.x;
+  float sum = 0.f;
+  for (int b = threadIdx.x; b < a.blocks; b += kNormThreads) sum += a.partial[(int64_t)si * a.blocks + b];
+  const float t = block_sum(sum, red);
+  if (threadIdx.x == 0) a.norms[si] = __builtin_sqrtf(t);
+}
+
+template <typename T, int NS, bool REF>
+hipError_t launch_slots(const NormArgs& a, int slot0, int groups, hipStream_t s) {
+  const dim3 grid((unsigned)a.blocks, (unsigned)groups);
+  hipLaunchKernelGGL((norms_partial_kernel<T, NS, REF>), grid, dim3(kNormThreads), 0, s, a, slot0);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_norms_t(const NormArgs& a, hipStream_t s) {
+  if (a.ref == nullptr) return launch_slots<T, 1, false>(a, 0, a.n, s);
+  hipError_t e = hipSuccess;
+  if (a.n >= 4) e = launch_slots<T, 4, true>(a, 0, a.n / 4, s);
+  if (e != hipSuccess) return e;
+  const int s0 = a.n / 4 * 4;
+  switch (a.n - s0) {
+    case 1: return launch_slots<T, 1, true>(a, s0, 1, s);
+    case 2: return launch_slots<T, 2, true>(a, s0, 1, s);
+    case 3: return launch_slots<T, 3, true>(a, s0, 1, s);
+  }
+  return hipSuccess;
 }
 
 }  // namespace
 
 hipError_t launch_norms(const NormArgs& a, ditango_dtype dt, hipStream_t s) {
   if (a.n <= 0) return hipSuccess;
-  if (a.blocks > 0) {
-    const dim3 grid((unsigned)a.blocks, (unsigned)a.n);
-    if (dt == DITANGO_BF16)
-      hipLaunchKernelGGL(norms_partial_kernel<__bf16>, grid, dim3(kNormThreads), 0, s, a);
-    else
-      hipLaunchKernelGGL(norms_partial_kernel<float>, grid, dim3(kNormThreads), 0, s, a);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(norms_final_kernel, dim3(1), dim3(kNormThreads), 0, s, a);
+  const hipError_t e = dt == DITANGO_BF16 ? launch_norms_t<__bf16>(a, s) : launch_norms_t<float>(a, s);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(norms_final_kernel, dim3(a.n), dim3(kNormThreads), 0, s, a);
   return hipGetLastError();
 }
 
