@@ -1,0 +1,82 @@
+"""GPU tests of the streaming kernels at the edges of their instances: the
+composition of float32 states over lists of 1 .. 17 slots, per-row weights
+written through LDS for partition counts around the 16 staged at a time, and
+state norms with a reference shared by up to four slots.
+
+Reference: torch in float64.  A float32 result here is a handful of products
+and a short sum (at most 64 terms, or a fixed tree over the rows): 1e-6 on
+weights, 1e-5 on composed outputs, 1e-5 relative on norms."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 8, 9, 16, 17])
+def test_merge_float32_lists(D, n):
+    import torch
+    from paper_2607_15650_amd import api
+    P, B, L, H = 18, 2, 13, 3                     # 78 rows: a partial last workgroup
+    g = torch.Generator(device="cuda").manual_seed(n)
+    st = torch.randn((P, B, L, H, D), generator=g, device="cuda")
+    lse = torch.randn((P, B, H, L), generator=g, device="cuda")
+    lse[:, 1, 2, 5] = float("-inf")               # a row without any state
+    slots = [(5 * i + 2) % P for i in range(n)]
+    for out_dt in (torch.float32, torch.bfloat16):
+        out = torch.full((B, L, H, D), 3.0, dtype=out_dt, device="cuda")
+        lo = torch.full((B, H, L), 3.0, device="cuda")
+        api.merge_states(st, lse, out, lo, slots=slots)
+        ll = lse[slots].double()
+        tot = torch.logsumexp(ll, 0)
+        w = torch.exp(ll - tot).nan_to_num(0.0)
+        ref = (st[slots].double() * w.permute(0, 1, 3, 2)[..., None]).sum(0)
+        tol = 1e-5 if out_dt == torch.float32 else 2.0 ** -8 * float(ref.abs().max())
+        assert float((out.double() - ref).abs().max()) <= tol
+        dead = torch.isneginf(tot)
+        assert bool(torch.isneginf(lo[dead]).all()) and float((lo.double() - tot)[~dead].abs().max()) <= 1e-5
+    # in place into the first listed slot
+    keep = ref
+    api.merge_states(st, lse, st[slots[0]], lse[slots[0]], slots=slots)
+    assert float((st[slots[0]].double() - keep).abs().max()) <= 1e-5
+
+
+@pytest.mark.parametrize("P", [1, 3, 8, 9, 15, 16, 17, 20, 33, 64])
+def test_weight_rows(P):
+    import torch
+    from paper_2607_15650_amd import api
+    for B, H, L in ((1, 1, 1), (1, 3, 171), (2, 5, 103)):     # 1, 513 and 1,030 rows of 512 per workgroup
+        g = torch.Generator(device="cuda").manual_seed(P)
+        lse = torch.randn((P, B, H, L), generator=g, device="cuda")
+        lse[P // 2, 0, 0, 0] = float("-inf")
+        lo = torch.logsumexp(lse.double(), 0).float()
+        w = torch.empty(P, device="cuda")
+        pad = torch.full((B * H * L * P + 64,), 9.0, device="cuda")
+        rows = pad[:B * H * L * P].view(B, H, L, P)
+        ws = torch.empty(api.contrib_workspace_bytes(B, H, L, P), dtype=torch.uint8, device="cuda")
+        api.contrib(lse, lo, w, ws, rows)
+        ref = torch.exp(lse.double() - lo.double()).nan_to_num(0.0).permute(1, 2, 3, 0)
+        assert float((rows.double() - ref).abs().max()) <= 1e-6
+        assert float((w.double() - ref.mean((0, 1, 2))).abs().max()) <= 1e-6
+        assert bool((pad[B * H * L * P:] == 9.0).all())
+        w2 = torch.empty(P, device="cuda")
+        api.contrib(lse, lo, w2, ws)
+        assert torch.equal(w, w2)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 7, 8])
+def test_norms_of_slots_sharing_a_reference(dtype, n):
+    import torch
+    from paper_2607_15650_amd import api
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    for B, L, H, D in ((1, 1, 1, 64), (1, 129, 4, 64), (2, 67, 3, 128)):   # 8, 4,128 and 6,432 chunks of 4,096
+        g = torch.Generator(device="cuda").manual_seed(n)
+        st = torch.randn((9, B, L, H, D), generator=g, device="cuda").to(dt)
+        ref = torch.randn((B, L, H, D), generator=g, device="cuda").to(dt)
+        slots = [(4 * i + 1) % 9 for i in range(n)]
+        ws = torch.empty(api.norms_workspace_bytes(B, H, D, L, n), dtype=torch.uint8, device="cuda")
+        for r in (ref, None):
+            got = torch.empty(n, device="cuda")
+            api.state_norms(st, got, ws, slots=slots, ref=r)
+            exp = torch.stack([(st[j].double() - (0.0 if r is None else r.double())).norm() for j in slots])
+            assert float(((got.double() - exp) / exp).abs().max()) <= 1e-5
