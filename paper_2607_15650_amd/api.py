@@ -137,6 +137,41 @@ def merge_states(out_states: torch.Tensor, lse_states: torch.Tensor, out: torch.
     _lib.check("ditango_merge_states", st)
 
 
+def compose_workspace(device="cuda") -> torch.Tensor:
+    """A zeroed workspace for ``compose``; it serves any number of calls, of
+    any sizes, that do not overlap."""
+    return torch.zeros(_lib.COMPOSE_WORKSPACE_BYTES, dtype=torch.uint8, device=device)
+
+
+def compose(out_states: torch.Tensor, lse_states: torch.Tensor, out: torch.Tensor, lse_out: Optional[torch.Tensor],
+            w_part: torch.Tensor, workspace: torch.Tensor, slots: Optional[Sequence[int]] = None) -> None:
+    """Composition of the listed slots (default: all) into ``out``/``lse_out``
+    and the listed slots' mean contribution weights into ``w_part``, in one
+    launch (ditango_compose).  ``workspace`` comes from compose_workspace."""
+    _dev(out_states, lse_states, out, lse_out, w_part, workspace)
+    P, B, q_len, H, D = out_states.shape
+    if tuple(lse_states.shape) != (P, B, H, q_len) or lse_states.dtype != torch.float32:
+        raise ValueError("lse_states must be float32 [P, B, H, q_len]")
+    if tuple(out.shape) != (B, q_len, H, D):
+        raise ValueError("out must be [B, q_len, H, D]")
+    if lse_out is not None and (tuple(lse_out.shape) != (B, H, q_len) or lse_out.dtype != torch.float32):
+        raise ValueError("lse_out must be float32 [B, H, q_len]")
+    if slots is None:
+        sl, n = None, P
+    else:
+        n = len(slots)
+        sl = (ctypes.c_int32 * n)(*[int(s) for s in slots])
+    if tuple(w_part.shape) != (n,) or w_part.dtype != torch.float32:
+        raise ValueError("w_part must be float32 [n_slots]")
+    if workspace.numel() * workspace.element_size() < _lib.COMPOSE_WORKSPACE_BYTES:
+        raise ValueError(f"workspace too small: need {_lib.COMPOSE_WORKSPACE_BYTES} bytes")
+    st = _lib.lib().ditango_compose(
+        out_states.data_ptr(), lse_states.data_ptr(), _dtype(out_states), P, sl, n,
+        B, H, D, q_len, out.data_ptr(), _dtype(out),
+        lse_out.data_ptr() if lse_out is not None else None, w_part.data_ptr(), workspace.data_ptr(), _stream())
+    _lib.check("ditango_compose", st)
+
+
 def contrib_workspace_bytes(B: int, H: int, q_len: int, P: int) -> int:
     return int(_lib.lib().ditango_contrib_workspace_bytes(B, H, q_len, P))
 

@@ -139,37 +139,82 @@ ditango_status ditango_attn_partition_states(
                                           out_states, dt, lse_states, stream);
 }
 
-ditango_status ditango_merge_states(
-    const void* out_states, const float* lse_states, ditango_dtype state_dt,
-    int P, const int32_t* slots, int n_slots,
-    int B, int H, int D, int64_t q_len,
-    void* out, ditango_dtype out_dt, float* lse_out, void* stream) {
+}  // extern "C"
+
+namespace {
+
+// Argument checks of the compositions; fills `a` (without weights).
+ditango_status merge_args(const void* out_states, const float* lse_states, ditango_dtype state_dt, int P,
+                          const int32_t* slots, int n_slots, int B, int H, int D, int64_t q_len, void* out,
+                          ditango_dtype out_dt, float* lse_out, MergeArgs* a) {
   if (!out_states || !lse_states || !out) return DITANGO_ERR_INVALID;
   if (!valid_dtype(state_dt) || !valid_dtype(out_dt)) return DITANGO_ERR_INVALID;
   if (B < 1 || H < 1 || q_len < 1 || P < 1) return DITANGO_ERR_INVALID;
   if (P > kMaxParts) return DITANGO_ERR_UNSUPPORTED;
   if (D != 64 && D != 128) return DITANGO_ERR_UNSUPPORTED;
-  MergeArgs a;
-  memset(&a, 0, sizeof(a));
+  memset(a, 0, sizeof(*a));
   if (slots == nullptr) {
     n_slots = P;
-    for (int j = 0; j < P; ++j) a.slots[j] = j;
+    for (int j = 0; j < P; ++j) a->slots[j] = j;
   } else {
     if (n_slots < 1 || n_slots > kMaxParts) return DITANGO_ERR_INVALID;
     for (int j = 0; j < n_slots; ++j) {
       if (slots[j] < 0 || slots[j] >= P) return DITANGO_ERR_INVALID;
-      a.slots[j] = slots[j];
+      a->slots[j] = slots[j];
     }
   }
-  a.states = out_states;
-  a.lse = lse_states;
-  a.out = out;
-  a.lse_out = lse_out;
-  a.q_len = q_len;
-  a.rows = (int64_t)B * q_len * H;
-  a.B = B;
-  a.H = H;
-  a.n = n_slots;
+  a->states = out_states;
+  a->lse = lse_states;
+  a->out = out;
+  a->lse_out = lse_out;
+  a->q_len = q_len;
+  a->rows = (int64_t)B * q_len * H;
+  a->B = B;
+  a->H = H;
+  a->n = n_slots;
+  return DITANGO_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+ditango_status ditango_merge_states(
+    const void* out_states, const float* lse_states, ditango_dtype state_dt,
+    int P, const int32_t* slots, int n_slots,
+    int B, int H, int D, int64_t q_len,
+    void* out, ditango_dtype out_dt, float* lse_out, void* stream) {
+  MergeArgs a;
+  const ditango_status st = merge_args(out_states, lse_states, state_dt, P, slots, n_slots, B, H, D, q_len, out, out_dt,
+                                       lse_out, &a);
+  if (st != DITANGO_OK) return st;
+  return from_hip(launch_merge(a, state_dt, out_dt, D, (hipStream_t)stream));
+}
+
+ditango_status ditango_compose(
+    const void* out_states, const float* lse_states, ditango_dtype state_dt,
+    int P, const int32_t* slots, int n_slots,
+    int B, int H, int D, int64_t q_len,
+    void* out, ditango_dtype out_dt, float* lse_out,
+    float* w_part, void* workspace, void* stream) {
+  MergeArgs a;
+  const ditango_status st = merge_args(out_states, lse_states, state_dt, P, slots, n_slots, B, H, D, q_len, out, out_dt,
+                                       lse_out, &a);
+  if (st != DITANGO_OK) return st;
+  if (!w_part || !workspace || ((uintptr_t)workspace & 255u) != 0) return DITANGO_ERR_INVALID;
+  // the weights are formed from the listed slots while the composition is
+  // being written: not in place
+  const size_t slot_bytes = (size_t)a.rows * D * (state_dt == DITANGO_F32 ? 4 : 2);
+  for (int j = 0; j < a.n; ++j) {
+    if (out == (const char*)out_states + (size_t)a.slots[j] * slot_bytes) return DITANGO_ERR_INVALID;
+    if (lse_out == lse_states + (size_t)a.slots[j] * a.rows) return DITANGO_ERR_INVALID;
+  }
+  if (a.rows > 0x7fffffffLL) return DITANGO_ERR_UNSUPPORTED;
+  a.n_wblocks = compose_wblocks(a.rows, a.n, &a.w_iters);
+  a.w_part = w_part;
+  a.w_sum = (uint64_t*)workspace;
+  a.w_count = (int*)(a.w_sum + kMaxParts);
+  static_assert(kMaxParts * sizeof(uint64_t) + sizeof(int) <= DITANGO_COMPOSE_WORKSPACE_BYTES, "workspace");
   return from_hip(launch_merge(a, state_dt, out_dt, D, (hipStream_t)stream));
 }
 

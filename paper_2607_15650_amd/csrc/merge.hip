@@ -77,6 +77,105 @@ __device__ __forceinline__ void store8(float* row, int ch, const f32x8& v) {
 constexpr int kMergeThreads = 64;      // small workgroups keep every CU evenly fed
 constexpr int kMergeBatch = 8;         // slots whose loads are in flight together
 
+__device__ __forceinline__ float wave_sum(float x) {
+#pragma unroll
+  for (int k = 32; k > 0; k >>= 1) x += __shfl_xor(x, k, 64);
+  return x;
+}
+
+// Composed log-sum-exp of a row's NMAX values (-inf past the list), which are
+// replaced by e^{LSE_j - M}; *sum is their sum.
+template <int NMAX>
+__device__ __forceinline__ float row_lse(float (&lv)[NMAX], float* sum) {
+  float mx = -INFINITY;
+#pragma unroll
+  for (int j = 0; j < NMAX; ++j) mx = fmaxf(mx, lv[j]);
+  float tot = 0.f;
+#pragma unroll
+  for (int j = 0; j < NMAX; ++j) {
+    lv[j] = mx == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((lv[j] - mx) * kLog2e);
+    tot += lv[j];
+  }
+  *sum = tot;
+  return tot > 0.f ? mx + __builtin_amdgcn_logf(tot) * kLn2 : -INFINITY;
+}
+
+// e^{LSE_j - LSE}, 0 where either is -inf
+__device__ __forceinline__ float weight_of(float lj, float lo) {
+  return lo != -INFINITY && lj != -INFINITY ? __builtin_amdgcn_exp2f((lj - lo) * kLog2e) : 0.f;
+}
+
+// rows of a lane whose loads are in flight together, by the slot bound
+constexpr int weight_rows(int nmax) { return nmax <= 8 ? 2 : 1; }
+
+// One weight workgroup (one wave) of a composition with weights: mean weights
+// of the listed slots over all rows, in one launch with the composition.  The
+// wave composes its rows' log-sum-exps itself (the composed ones are being
+// written by other workgroups), sums each slot's weights over its rows in
+// float32 and adds the sums, in units of 2^-32, to 64-bit integers: integer
+// sums do not depend on their order, so the means are the same bits on every
+// run.  (A weight lies in [0, 1] and is 0 where a log-sum-exp is not finite,
+// so up to 2^31 rows cannot overflow.)  The wave that finds all others
+// finished writes the means and leaves sums and counter at zero for the next
+// launch.
+//
+// Sums and counter are touched with device-scope atomics only: the XCDs' L2
+// caches are not coherent with each other, and an atomic's result is in none
+// of them.  A wave's sums are added (vmcnt) before it counts itself finished.
+template <int NMAX>
+__device__ void weights_block(const MergeArgs& a) {
+  constexpr int R = weight_rows(NMAX);
+  const int lane = threadIdx.x;
+  const int n = a.n;
+  const int64_t n_rows = a.rows;
+  float acc[NMAX];
+#pragma unroll
+  for (int j = 0; j < NMAX; ++j) acc[j] = 0.f;
+  for (int it = 0; it < a.w_iters; ++it) {
+    const int64_t base = ((int64_t)blockIdx.x * a.w_iters + it) * (R * kMergeThreads) + lane;
+    float lv[R][NMAX];
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const int64_t r = base + i * kMergeThreads;
+      const int64_t rc = r < n_rows ? r : n_rows - 1;
+#pragma unroll
+      for (int j = 0; j < NMAX; ++j) {
+        lv[i][j] = -INFINITY;
+        if (j < n) lv[i][j] = a.lse[(int64_t)a.slots[j] * n_rows + rc];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const bool ok = base + i * kMergeThreads < n_rows;
+      float e[NMAX], tot;
+#pragma unroll
+      for (int j = 0; j < NMAX; ++j) e[j] = lv[i][j];
+      const float lo = row_lse<NMAX>(e, &tot);
+#pragma unroll
+      for (int j = 0; j < NMAX; ++j)
+        if (j < n) acc[j] += ok ? weight_of(lv[i][j], lo) : 0.f;
+    }
+  }
+  float mine = 0.f;                      // lane j: the sum of slot j
+#pragma unroll
+  for (int j = 0; j < NMAX; ++j)
+    if (j < n) {
+      const float t = wave_sum(acc[j]);
+      mine = lane == j ? t : mine;
+    }
+  if (lane < n)
+    __hip_atomic_fetch_add(a.w_sum + lane, (uint64_t)(mine * 4294967296.f), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  int done = 0;
+  if (lane == 0) done = __hip_atomic_fetch_add(a.w_count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (__builtin_amdgcn_readfirstlane(done) != a.n_wblocks - 1) return;
+  if (lane < n) {
+    const uint64_t sum = __hip_atomic_exchange(a.w_sum + lane, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    a.w_part[lane] = (float)((double)sum * (1.0 / 4294967296.0) / (double)n_rows);
+  }
+  if (lane == 0) __hip_atomic_store(a.w_count, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Each thread owns 8 elements of one row (row = (b*q_len + r)*H + h,
 // rows contiguous in every slot), so the CPR = D/8 lanes of a row are
 // consecutive lanes of one wave.  The thread first issues the loads of the
@@ -99,8 +198,12 @@ template <typename TS, typename TO, int D, int NMAX, bool IDX32>
 __global__ __launch_bounds__(kMergeThreads) void merge_kernel(const MergeArgs a) {
   constexpr int CPR = D / 8;                      // chunks (lanes) per row
   using CK = Chunk8<TS, D>;
+  if ((int)blockIdx.x < a.n_wblocks) {
+    weights_block<NMAX>(a);
+    return;
+  }
   const int n = a.n;
-  const int64_t c = (int64_t)blockIdx.x * kMergeThreads + threadIdx.x;
+  const int64_t c = (int64_t)(blockIdx.x - a.n_wblocks) * kMergeThreads + threadIdx.x;
   const bool live = c < a.rows * CPR;
   const int64_t row = live ? c / CPR : 0;
   const int ch = (int)(c % CPR);
@@ -144,17 +247,9 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(const MergeArgs a)
     if (u < n) x[u] = CK::load(st + (int64_t)sl[u] * slot_elems, ch);
   }
 
-  float mx = -INFINITY;
-#pragma unroll
-  for (int j = 0; j < NMAX; ++j) mx = fmaxf(mx, lv[j]);
-  float tot = 0.f;
-#pragma unroll
-  for (int j = 0; j < NMAX; ++j) {
-    lv[j] = mx == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((lv[j] - mx) * kLog2e);
-    tot += lv[j];
-  }
+  float tot;
+  const float lse = row_lse<NMAX>(lv, &tot);
   const float inv = tot > 0.f ? 1.0f / tot : 0.f;
-  const float lse = tot > 0.f ? mx + __builtin_amdgcn_logf(tot) * kLn2 : -INFINITY;
   auto weight = [&](int j) { return lv[j] * inv; };
   f32x8 acc = f32x8{};
 #pragma unroll
@@ -195,8 +290,8 @@ template <typename TS, typename TO, int D>
 hipError_t launch_merge_t(const MergeArgs& a, hipStream_t s) {
   const int64_t blocks = (a.rows * (D / 8) + kMergeThreads - 1) / kMergeThreads;
   if (blocks == 0) return hipSuccess;
-  if (blocks > 0x7fffffff) return hipErrorInvalidConfiguration;
-  const dim3 g((unsigned)blocks), t(kMergeThreads);
+  if (blocks + a.n_wblocks > 0x7fffffff) return hipErrorInvalidConfiguration;
+  const dim3 g((unsigned)(blocks + a.n_wblocks)), t(kMergeThreads);
   if (a.rows < 0x7fffffffLL && (int64_t)a.B * a.H * a.q_len < 0x7fffffffLL)
     launch_merge_n<TS, TO, D, true>(a, g, t, s);
   else
@@ -222,12 +317,6 @@ constexpr int kContribThreads = 256;
 constexpr int kContribRowsPerThread = 2;
 constexpr int kContribRowsPerBlock = kContribThreads * kContribRowsPerThread;
 constexpr int kContribWaves = kContribThreads / 64;
-
-__device__ __forceinline__ float wave_sum(float x) {
-#pragma unroll
-  for (int k = 32; k > 0; k >>= 1) x += __shfl_xor(x, k, 64);
-  return x;
-}
 
 // Per-row weights are written through LDS, 16 partitions at a time: a wave's
 // 64 rows x P floats are consecutive in memory, and its lanes write them in
@@ -275,9 +364,7 @@ __global__ __launch_bounds__(kContribThreads) void contrib_partial_kernel(const 
 #pragma unroll
     for (int j = 0; j < PMAX; ++j) {
       if (j < P) {
-        float w = 0.f;
-        if (ok && lo[i] != -INFINITY && lj[i][j] != -INFINITY)
-          w = __builtin_amdgcn_exp2f((lj[i][j] - lo[i]) * kLog2e);
+        const float w = ok ? weight_of(lj[i][j], lo[i]) : 0.f;
         acc[j] += w;
         lj[i][j] = w;
       }
@@ -369,6 +456,22 @@ hipError_t launch_merge(const MergeArgs& a, ditango_dtype sdt, ditango_dtype odt
   if (sdt == DITANGO_F32 && odt == DITANGO_F32) return launch_merge_d<float, float>(a, D, s);
   if (sdt == DITANGO_F32 && odt == DITANGO_BF16) return launch_merge_d<float, __bf16>(a, D, s);
   return hipErrorInvalidValue;
+}
+
+// Up to 128 weight workgroups, each taking as many rounds of rows as that
+// needs.  They come first in the grid and run beside the composition; what
+// limits their number is the additions to one line of memory from all XCDs:
+// 9,450 rows x 40 heads x 8 slots, composition alone 140 us, with weights
+// 141 / 143 / 148 / 160 us with up to 128 / 256 / 512 / 1,024 of them (149
+// with the two weight kernels after it); 8,192 x 24 x 16: 146 alone, 148 /
+// 148 / 151 / 165 (157); 2,048 x 12 x 8 at D=64: 5.9 alone, 9.6 (13.0).
+constexpr int kComposeBlocks = 128;
+int compose_wblocks(int64_t n_rows, int n, int* iters) {
+  const int64_t per = kMergeThreads * weight_rows(n);
+  const int64_t rounds = (n_rows + per - 1) / per;
+  const int64_t it = (rounds + kComposeBlocks - 1) / kComposeBlocks;
+  *iters = (int)it;
+  return (int)((rounds + it - 1) / it);
 }
 
 int64_t contrib_blocks(int64_t n_rows) { return (n_rows + kContribRowsPerBlock - 1) / kContribRowsPerBlock; }

@@ -145,13 +145,9 @@ class GroupedSelectiveAttention:
         slots = [grp[0] for grp in self.groups] + [self.q]
         out = torch.empty((self.B, self.L, self.H, self.D), dtype=self.dtype, device=self.device)
         lse = torch.empty((self.B, self.H, self.L), dtype=torch.float32, device=self.device)
-        api.merge_states(self.out, self.lse, out, lse, slots=slots)
-        # weights of the live groups: contrib over a compact copy of their LSE slots
-        lse_live = self.lse[slots].contiguous()
-        n = len(slots)
-        if self._ws is None or self._ws.numel() < api.contrib_workspace_bytes(self.B, self.H, self.L, n):
-            self._ws = torch.empty(max(16, api.contrib_workspace_bytes(self.B, self.H, self.L, self.P)),
-                                   dtype=torch.uint8, device=self.device)
-        w = torch.empty(n, dtype=torch.float32, device=self.device)
-        api.contrib(lse_live, lse, w, self._ws)
+        # composition and the weights of the live groups
+        w = torch.empty(len(slots), dtype=torch.float32, device=self.device)
+        if self._ws is None:
+            self._ws = api.compose_workspace(self.device)
+        api.compose(self.out, self.lse, out, lse, w, self._ws, slots=slots)
         return out, lse, w

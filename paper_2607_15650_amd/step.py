@@ -47,7 +47,7 @@ class SelectiveAttention:
         self.state_dtype = state_dtype if state_dtype is not None else dtype
         self.device = device
         self.caches = {}
-        self._ws = {}
+        self._ws = None
         self._attn_ws = AttnWorkspace(device)
 
     def cache(self, qb: int) -> StateCache:
@@ -76,11 +76,8 @@ class SelectiveAttention:
         L = e - a
         out = torch.empty((self.B, L, self.H, self.D), dtype=self.dtype, device=self.device)
         lse = torch.empty((self.B, self.H, L), dtype=torch.float32, device=self.device)
-        api.merge_states(c.out, c.lse, out, lse)
         w_part = torch.empty(self.P, dtype=torch.float32, device=self.device)
-        key = (self.B, self.H, L, self.P)
-        if key not in self._ws:
-            self._ws[key] = torch.empty(max(16, api.contrib_workspace_bytes(*key)), dtype=torch.uint8,
-                                        device=self.device)
-        api.contrib(c.lse, lse, w_part, self._ws[key])
+        if self._ws is None:
+            self._ws = api.compose_workspace(self.device)
+        api.compose(c.out, c.lse, out, lse, w_part, self._ws)
         return out, lse, w_part

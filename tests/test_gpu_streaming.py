@@ -1,7 +1,8 @@
 """GPU tests of the streaming kernels at the edges of their instances: the
 composition of float32 states over lists of 1 .. 17 slots, per-row weights
 written through LDS for partition counts around the 16 staged at a time, and
-state norms with a reference shared by up to four slots.
+state norms with a reference shared by up to four slots; the composition with
+weights in one launch against the composition and the weights on their own.
 
 Reference: torch in float64.  A float32 result here is a handful of products
 and a short sum (at most 64 terms, or a fixed tree over the rows): 1e-6 on
@@ -80,3 +81,66 @@ def test_norms_of_slots_sharing_a_reference(dtype, n):
             api.state_norms(st, got, ws, slots=slots, ref=r)
             exp = torch.stack([(st[j].double() - (0.0 if r is None else r.double())).norm() for j in slots])
             assert float(((got.double() - exp) / exp).abs().max()) <= 1e-5
+
+
+@pytest.mark.parametrize("dtype,D,B,L,H,P,slots", [
+    ("bf16", 128, 1, 1, 1, 1, None),                      # one row, one weight workgroup
+    ("bf16", 64, 2, 43, 3, 8, [6, 1, 3]),                 # 258 rows: a partial third workgroup of 128
+    ("f32", 64, 1, 1025, 16, 4, None),                    # 16,400 rows: 129 rounds, two per workgroup
+    ("bf16", 128, 2, 900, 10, 9, [8, 0, 2, 4, 1, 7, 3, 5, 6]),   # 64 rows per round beyond 8 slots
+    ("f32", 128, 1, 130, 2, 20, None),
+    ("bf16", 64, 1, 70, 2, 64, None),
+])
+def test_compose_is_merge_and_weights(dtype, D, B, L, H, P, slots):
+    import torch
+    from paper_2607_15650_amd import api
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(L)
+    st = torch.randn((P, B, L, H, D), generator=g, device="cuda").to(dt)
+    lse = torch.randn((P, B, H, L), generator=g, device="cuda")
+    lse[:, 0, 0, 0] = float("-inf")                       # a row without any state
+    lse[P - 1, 0, H - 1, L // 2] = float("-inf")
+    listed = list(range(P)) if slots is None else slots
+    out, ref = (torch.full((B, L, H, D), 3.0, dtype=dt, device="cuda") for _ in range(2))
+    lo, lref = (torch.full((B, H, L), 3.0, device="cuda") for _ in range(2))
+    api.merge_states(st, lse, ref, lref, slots=slots)
+    ll = lse[listed].double()
+    w64 = torch.exp(ll - torch.logsumexp(ll, 0)).nan_to_num(0.0).mean((1, 2, 3))
+    ws = api.compose_workspace()
+    first = None
+    for _ in range(3):                                    # one workspace, left as it was found
+        w = torch.full((len(listed),), 7.0, device="cuda")
+        out.fill_(3.0)
+        lo.fill_(3.0)
+        api.compose(st, lse, out, lo, w, ws, slots=slots)
+        assert torch.equal(out, ref) and torch.equal(lo.view(torch.int32), lref.view(torch.int32))
+        assert float((w.double() - w64).abs().max()) <= 1e-6
+        assert int(ws.to(torch.int32).sum()) == 0
+        first = w.clone() if first is None else first
+        assert torch.equal(w, first)
+    api.compose(st, lse, out, None, w, ws, slots=slots)   # without the composed log-sum-exps
+    assert torch.equal(w, first) and torch.equal(out, ref)
+
+
+def test_compose_captured_in_a_graph():
+    import torch
+    from paper_2607_15650_amd import api
+    P, B, L, H, D = 5, 1, 300, 4, 128
+    g = torch.Generator(device="cuda").manual_seed(1)
+    st = torch.randn((P, B, L, H, D), generator=g, device="cuda").to(torch.bfloat16)
+    lse = torch.randn((P, B, H, L), generator=g, device="cuda")
+    out = torch.empty((B, L, H, D), dtype=torch.bfloat16, device="cuda")
+    lo, w, ws = torch.empty((B, H, L), device="cuda"), torch.empty(P, device="cuda"), api.compose_workspace()
+    api.compose(st, lse, out, lo, w, ws)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        api.compose(st, lse, out, lo, w, ws)
+    for i in range(4):
+        lse.add_(torch.randn((P, B, H, L), generator=g, device="cuda"))
+        w.fill_(9.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        replayed = (out.clone(), lo.clone(), w.clone())
+        api.compose(st, lse, out, lo, w, ws)              # eager work on the same workspace between
+        assert all(torch.equal(a, b) for a, b in zip(replayed, (out, lo, w))), i
