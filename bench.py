@@ -129,17 +129,22 @@ def attn_mode(ws):
 
 
 def attn_kernels(ws, w, select):
-    """The kernels of one attention launch: the hand-scheduled kernel at
-    D=128, and at D=64 for launches of at least four rounds of 256-row tasks
-    (shorter D=64 launches run the compiled kernel)."""
+    """The kernels of one attention launch: the hand-scheduled kernel, except
+    in D=64 launches of partitions of unequal lengths or whose 384-row tasks
+    fit one round (d64_use_asm in attn_bf16.hip); the queue counters serve
+    launches of at least eight rounds, or of unequal partitions."""
     import torch
     mode = attn_mode(ws)
     cus = torch.cuda.get_device_properties(0).multi_processor_count
-    tasks = -(-w.q_len // 256) * w.H * w.B * len(select)
-    asm = w.D == 128 or tasks >= 4 * cus
+    heads = w.H * w.B * len(select)
+    tasks = -(-w.q_len // 256) * heads
+    lens = [w.offsets[j + 1] - w.offsets[j] for j in select]
+    equal = 8 * (max(lens) - min(lens)) <= max(lens)
+    one_round = -(-w.q_len // 384) * heads <= cus
+    asm = w.D == 128 or tasks >= 4 * cus or (equal and not (one_round and 8 * tasks >= 11 * cus))
     k = f"attn_bf16_asm_kernel<{w.D}>" if asm else f"attn_bf16_kernel<{w.D}>"
-    return {"static": k, "queue": f"attn_queue_reset_kernel + {k}",
-            "split": f"attn_queue_reset_kernel + {k} + attn_split_fixup_kernel"}[mode]
+    reset = "attn_queue_reset_kernel + " if tasks >= 8 * cus or not equal else ""
+    return {"static": k, "queue": reset + k, "split": f"{reset}{k} + attn_split_fixup_kernel"}[mode]
 
 
 def attn_counters(w, select, mode):

@@ -110,11 +110,13 @@ ditango_status ditango_attn_partition_states_ex(
  * attention_state; split partial states are composed by Eq. composition).
  * A launch is a set of tasks (query tile x head x batch x selected
  * partition) of which the GPU runs a fixed number at a time.
- *  - Balancing: the first 256 bytes of the workspace hold queue counters
- *    (zeroed by a small kernel on `stream` before a launch that claims any
- *    task).  Most tasks run where the hardware places them; the last ones
- *    are claimed from the counters, so that XCDs that run faster take more
- *    of them.
+ *  - Balancing, of launches of at least eight rounds or of partitions of
+ *    unequal lengths: the first 256 bytes of the workspace hold queue
+ *    counters (zeroed by a small kernel on `stream` before a launch that
+ *    claims any task).  Most tasks run where the hardware places them; the
+ *    last ones are claimed from the counters, so that XCDs that run faster
+ *    take more of them.  Shorter launches gain nothing from it and run
+ *    every task where the hardware places it.
  *  - Tail split: when the last round is partly filled, the launch has at
  *    most 4 full rounds before it (after more, balancing evens out its
  *    end) and an estimate of the round's cost in key tiles says a split

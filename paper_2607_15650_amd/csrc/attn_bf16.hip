@@ -34,8 +34,8 @@
 //   (4 consecutive keys x 4 units) hit 16 distinct 16-byte bank groups.
 //
 // Two kernels
-//   Launches at D=128, and at D=64 when they run at least four rounds of
-//   tasks, use attn_bf16_asm_kernel: four waves, one per SIMD, two 32-row
+//   Launches at D=128, and most at D=64 (d64_use_asm), use
+//   attn_bf16_asm_kernel: four waves, one per SIMD, two 32-row
 //   query blocks per wave so that every LDS fragment feeds two MFMAs, the
 //   O^T accumulators and Q^T in AGPRs, and a key loop written as gfx950
 //   assembly by gen_attn_loop.py (attn_d128_loop.inc, attn_d64_loop.inc).
@@ -43,9 +43,9 @@
 //   test); a workgroup whose row sums end above 2^40 or NaN runs its task
 //   again in the checked loop, which follows the running-maximum rule below
 //   and agrees with the fast loop bit for bit wherever the fast one is kept.
-//   The compiled kernel attn_bf16_kernel (the pipeline below) runs the
-//   other launches: short D=64 launches, and partitions whose bytes for one
-//   head reach the tile loads' 32-bit bounds.
+//   The compiled kernel attn_bf16_kernel (the pipeline below) runs the other
+//   launches, and those with a partition whose bytes for one head reach the
+//   tile loads' 32-bit bounds.
 //
 // Pipeline of the compiled kernel
 //   D=128 (two waves per SIMD): iteration i computes the scores of tile i+1
@@ -155,9 +155,13 @@ __device__ __forceinline__ void store4(float* p, const f32x4& x) { *(f32x4*)p = 
 // n_static / 8 positions run static (workgroup b: position b / 8 of list
 // b % 8).  The rest of list x is claimed through two counters: queue x for
 // its main tasks, queue 8 + x for its split units.
+// A position past the list's end (a launch without queues runs as many
+// positions of every list as the longest has) gives -1.
 __device__ __forceinline__ int list_unit(const AttnArgs& a, int x, int t) {
   const int lm = xcd_len(x, a.n_main);
-  return t < lm ? xcd_first(x, a.n_main) + t : a.n_main + xcd_first(x, a.n_split * a.split_f) + (t - lm);
+  const int n_tail = a.n_split * a.split_f;
+  if (t < lm) return xcd_first(x, a.n_main) + t;
+  return t - lm < xcd_len(x, n_tail) ? a.n_main + xcd_first(x, n_tail) + (t - lm) : -1;
 }
 // first list position and length handed out by queue q (0..15)
 __device__ __forceinline__ void queue_range(const AttnArgs& a, int q, int* first, int* len) {
@@ -257,8 +261,8 @@ __global__ __launch_bounds__(NW * 64, WPE) void attn_bf16_kernel(const AttnArgs 
     }
     __syncthreads();
     u = __builtin_amdgcn_readfirstlane(*claimed);
-    if (u < 0) return;
   }
+  if (u < 0) return;
   int task = u, part = -1;
   if (u >= a.n_main) {
     task = a.n_main + (u - a.n_main) / a.split_f;
@@ -746,8 +750,8 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_asm_kernel(const AttnArgs a)
     }
     __syncthreads();
     u = __builtin_amdgcn_readfirstlane(*claimed);
-    if (u < 0) return;
   }
+  if (u < 0) return;
   int task = u, part = -1;
   if (u >= a.n_main) {
     task = a.n_main + (u - a.n_main) / a.split_f;
@@ -1045,6 +1049,19 @@ __global__ __launch_bounds__(64) void attn_queue_reset_kernel(int* queue) {
 #ifndef DITANGO_DYN_ROUNDS
 #define DITANGO_DYN_ROUNDS 2
 #endif
+// Launches of at least this many rounds, or of unequal tasks, claim their
+// last ones.
+constexpr int64_t kDynMinRounds = 8;
+
+// whether the selected partitions' lengths are within an eighth of the longest
+inline bool equal_lengths(const AttnArgs& a) {
+  int64_t lo = INT64_MAX, hi = 0;
+  for (int j = 0; j < a.n_sel; ++j) {
+    lo = a.kv_len[j] < lo ? a.kv_len[j] : lo;
+    hi = a.kv_len[j] > hi ? a.kv_len[j] : hi;
+  }
+  return 8 * (hi - lo) <= hi;
+}
 
 // Launch plan of one bf16 launch: resident workgroup slots on the current
 // device, the tail split factor and number of split tasks, and the workspace
@@ -1138,7 +1155,6 @@ hipError_t launch_cfg(const AttnArgs& a0, void* ws, size_t ws_bytes, hipStream_t
   a.queue = nullptr;
   int64_t grid = nblk;
   if (queued) {
-    a.queue = (int*)ws;
     if (p.f > 1 && ws_bytes >= p.bytes) {
       a.n_main = (int)(nblk - p.n_split);
       a.n_split = (int)p.n_split;
@@ -1146,29 +1162,45 @@ hipError_t launch_cfg(const AttnArgs& a0, void* ws, size_t ws_bytes, hipStream_t
       a.part_out = (float*)((char*)ws + kQueueBytes);
       a.part_lse = (float*)((char*)a.part_out + align256((size_t)p.n_split * p.f * K::BM * D * sizeof(float)));
     }
-    // static share: the first positions of every XCD queue, all but its
-    // last DITANGO_DYN_ROUNDS rounds and at least the first round (which
-    // starts at once and gains nothing from claiming); as many extra
-    // workgroups as dynamic units, up to one round, let the faster XCDs
-    // take units from the slower ones' queues
-    const int64_t per_xcd = p.slots / 8 > 0 ? p.slots / 8 : 1;
+    // A launch of few rounds of equal tasks runs every position static: the
+    // counters' reset and the claims cost it 3-10 us, and there is no spread
+    // of finish times yet for them to even out (one card, static / claimed:
+    // 768 tasks of 32 tiles at D=64 106.2 / 111.8 us, 672 at D=128 152.7 /
+    // 163.4, 1,152 of 64 tiles at D=128 476 / 479, 2,048 of 128 tiles 1,578 /
+    // 1,585).  After many rounds the XCDs' speeds tell (2,720 tasks of 32
+    // tiles at D=128 593 / 588 us, 4,440 of 148 tiles 4,020 / 3,951, 2,832 of
+    // 233 tiles at D=64 2,568 / 2,427).  Partitions of unequal lengths make
+    // the XCDs' lists unequal work, whatever their number.
     const int64_t n_tail = (int64_t)a.n_split * a.split_f;
-    int64_t min_len = INT64_MAX;
+    int64_t min_len = INT64_MAX, max_len = 0;
     for (int x = 0; x < 8; ++x) {
       const int64_t len = (a.n_main >> 3) + (x < (a.n_main & 7) ? 1 : 0) + (n_tail >> 3) + (x < (n_tail & 7) ? 1 : 0);
       min_len = len < min_len ? len : min_len;
+      max_len = len > max_len ? len : max_len;
     }
-    int64_t st = min_len - DITANGO_DYN_ROUNDS * per_xcd;
-    const int64_t first = min_len < per_xcd ? min_len : per_xcd;
-    st = st > first ? st : first;
-    const int64_t n_units = (int64_t)a.n_main + n_tail;
-    const int64_t n_dyn = n_units - 8 * st;
-    a.n_static = (int)(8 * st);
-    grid = n_units + (n_dyn < p.slots ? n_dyn : p.slots);
-    if (n_dyn > 0) {
-      hipLaunchKernelGGL(attn_queue_reset_kernel, dim3(1), dim3(64), 0, s, a.queue);
-      const hipError_t e = hipGetLastError();
-      if (e != hipSuccess) return e;
+    if (nblk < kDynMinRounds * p.slots && equal_lengths(a)) {
+      a.n_static = (int)(8 * max_len);
+      grid = 8 * max_len;
+    } else {
+      // static share: the first positions of every XCD queue, all but its
+      // last DITANGO_DYN_ROUNDS rounds and at least the first round (which
+      // starts at once and gains nothing from claiming); as many extra
+      // workgroups as dynamic units, up to one round, let the faster XCDs
+      // take units from the slower ones' queues
+      const int64_t per_xcd = p.slots / 8 > 0 ? p.slots / 8 : 1;
+      int64_t st = min_len - DITANGO_DYN_ROUNDS * per_xcd;
+      const int64_t first = min_len < per_xcd ? min_len : per_xcd;
+      st = st > first ? st : first;
+      const int64_t n_units = (int64_t)a.n_main + n_tail;
+      const int64_t n_dyn = n_units - 8 * st;
+      a.queue = (int*)ws;
+      a.n_static = (int)(8 * st);
+      grid = n_units + (n_dyn < p.slots ? n_dyn : p.slots);
+      if (n_dyn > 0) {
+        hipLaunchKernelGGL(attn_queue_reset_kernel, dim3(1), dim3(64), 0, s, a.queue);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+      }
     }
   }
   K::launch(dim3((unsigned)grid), s, a);
@@ -1190,21 +1222,33 @@ inline bool asm_fits(const AttnArgs& a, int D) {
   return true;
 }
 
-// Which D=64 kernel a launch runs.  At D=64 the softmax's VALU work per MFMA
-// doubles and the hand-scheduled form gains little per tile (4 % at the
-// 118,800-token, 48-head shape), while its 256-row query tiles make more
-// tasks than the compiled kernel's 384-row ones: a launch that the compiled
-// kernel runs in one round can take two (the 16,384-token, 12-head reuse
-// launch: 288 tasks on 256 CUs against 216, 66.6 against 56 us).  So the
-// hand-scheduled kernel runs only launches of at least four rounds.
+// Which D=64 kernel a launch runs: the hand-scheduled one (256 rows per task)
+// from four rounds on, and in shorter launches of equal partitions (one card,
+// static / with the workspace, compiled kernel against this one: 2,048 rows x
+// 12 heads, 3 partitions of 2,048 keys 62.6 / 65.4 against 66.7 / 55.8 us, 1
+// partition 50.0 / 37.3 against 29.6, 8 partitions 163.8 / 153.6 against
+// 104.5; 1,639 x 3, 6 partitions 42.1 / 39.1 against 28.2; 1,000 x 40, 5
+// partitions 96.6 / 101.6 against 81.7 / 80.6), with two exceptions:
+//  - the compiled kernel's 384-row tasks fit one round of which 256-row tasks
+//    would make about one and a half: 6,144 x 8, 2 partitions of 2,048 keys
+//    64.0 against 65.9 us, 1,536 x 20, 3 of 2,048 59.6 against 61.0, 3,072 x
+//    8, 4 of 512 23.9 against 24.7;
+//  - partitions of unequal lengths, which stay with the compiled kernel and
+//    the split tail that goes with its 384-row tasks (6,244 x 8, 700 and
+//    1,234 keys: 54.1 us split, 48.9 here; 9,000 x 6, 700 and 400 keys: 47.6
+//    against 33.3).
 inline bool d64_use_asm(const AttnArgs& a) {
   if (!asm_fits(a, 64)) return false;
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
       cus <= 0)
     return false;
-  const int64_t tasks = (a.q_len + AsmCfg<64>::BM - 1) / AsmCfg<64>::BM * a.H * a.B * a.n_sel;
-  return tasks >= 4 * (int64_t)cus;
+  const int64_t heads = (int64_t)a.H * a.B * a.n_sel;
+  const int64_t tasks = (a.q_len + AsmCfg<64>::BM - 1) / AsmCfg<64>::BM * heads;
+  if (tasks >= 4 * (int64_t)cus) return true;
+  constexpr int kCompiledRows = 384;
+  const bool one_round = (a.q_len + kCompiledRows - 1) / kCompiledRows * heads <= cus;
+  return equal_lengths(a) && !(one_round && 8 * tasks >= 11 * (int64_t)cus);
 }
 
 }  // namespace
@@ -1224,7 +1268,7 @@ inline bool d64_use_asm(const AttnArgs& a) {
 #endif
 // Both head dims run the hand-scheduled kernel (attn_bf16_asm_kernel) unless
 // built with DITANGO_ASM=0, or a partition is too long for its 32-bit
-// tile-load bounds, or (D=64) the launch is short (d64_use_asm).
+// tile-load bounds, or (D=64) d64_use_asm prefers the compiled one.
 #ifndef DITANGO_ASM
 #define DITANGO_ASM 1
 #endif

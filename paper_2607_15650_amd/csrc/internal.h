@@ -37,16 +37,16 @@ struct AttnArgs {
   int split_f;
   float* part_out;          // [n_split * split_f][rows per workgroup][D]
   float* part_lse;          // [n_split * split_f][rows per workgroup]
-  // Balancing over the XCDs (bf16 kernel, with a workspace).  The units of
-  // work (main tasks, then split units) are dealt into 8 lists, one per
-  // XCD: list x holds the x-th contiguous eighth of the main tasks, then the
-  // x-th eighth of the split units.  Workgroups [0, n_static) run fixed
-  // units: workgroup b position b / 8 of list b % 8.  Every later workgroup
-  // claims one unit from the queue counters of the positions past
+  // Assignment to the XCDs (bf16 kernel).  The units of work (main tasks,
+  // then split units) are dealt into 8 lists, one per XCD: list x holds the
+  // x-th contiguous eighth of the main tasks, then the x-th eighth of the
+  // split units.  Workgroups [0, n_static) run fixed units: workgroup b
+  // position b / 8 of list b % 8 (nothing past the list's end).  Every later
+  // workgroup claims one unit from the queue counters of the positions past
   // n_static / 8 (queue x: list x's main tasks, queue 8 + x: its split
   // units): main tasks anywhere before split units, its own XCD's first; it
   // exits when all are exhausted.  queue = null: no queues, every workgroup
-  // is static (n_static = n_main, no split units).
+  // is static.
   int n_static;
   int* queue;               // kQueueInts counters, zeroed before the launch
 };

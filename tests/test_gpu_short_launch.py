@@ -1,0 +1,59 @@
+"""Launches of few rounds at both head dims: static over the XCDs' lists with
+a split tail (lists of unequal length among them), the hand-scheduled D=64
+kernel in launches of less than a round, and balanced launches of more than
+eight rounds, against the static launch without a workspace (bit for bit when
+unsplit) and against float64.
+
+Tolerances: bf16 states 1e-2 (unit-variance inputs, P V in bf16), LSE 2e-3."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+# (D, H, q_len, partition lengths)
+CASES = [
+    (64, 1, 1, [1]),
+    (64, 3, 257, [65, 64, 63]),                    # 18 tasks: lists of 3 and 2
+    (64, 5, 700, [130, 129, 128, 127, 126]),       # 75 tasks
+    (64, 10, 4096, [520, 519]),                    # 320 tasks of 9 tiles: a round and a quarter, split or not
+    (64, 11, 3000, [1100, 1050]),                  # 264 tasks of 18 tiles: 8 more than a round
+    (128, 11, 3000, [1100, 1050]),
+    (128, 3, 257, [65, 64, 63]),
+    (64, 12, 3800, [70, 64, 66, 65, 64, 63, 64, 64, 70, 68, 64, 66]),   # 2,160 tasks: claimed
+    (128, 12, 3800, [70, 64, 66, 65, 64, 63, 64, 64, 70, 68, 64, 66]),
+]
+
+
+@pytest.mark.parametrize("D,H,q_len,lens", CASES)
+def test_launches_match_static_and_float64(D, H, q_len, lens):
+    import torch
+    from paper_2607_15650_amd import api
+    P = len(lens)
+    offs = [sum(lens[:j]) for j in range(P + 1)]
+    g = torch.Generator(device="cuda").manual_seed(q_len)
+    q, k, v = (torch.randn((1, n, H, D), generator=g, device="cuda").to(torch.bfloat16)
+               for n in (q_len, offs[-1], offs[-1]))
+    sel = [1] * P
+    need = api.attn_workspace_bytes(torch.bfloat16, 1, H, D, q_len, offs, sel)
+
+    def launch(n):
+        ws = None if n is None else torch.full((n,), 0x5A, dtype=torch.uint8, device="cuda")
+        out = torch.full((P, 1, q_len, H, D), 9.0, dtype=torch.bfloat16, device="cuda")
+        lse = torch.full((P, 1, H, q_len), 9.0, device="cuda")
+        api.attn_partition_states(q, k, v, offs, sel, D ** -0.5, out, lse, ws)
+        return out, lse
+
+    static = launch(None)
+    unsplit = launch(256)
+    assert torch.equal(static[0], unsplit[0]) and torch.equal(static[1], unsplit[1])
+    full = launch(need)
+    for j in range(P):
+        for h in range(0, H, 5):
+            s = torch.mm(q[0, :, h].double(), k[0, offs[j]:offs[j + 1], h].double().t().contiguous()) * D ** -0.5
+            lse = torch.logsumexp(s, 1)
+            ref = torch.mm((s - lse[:, None]).exp(), v[0, offs[j]:offs[j + 1], h].double())
+            # few keys: a row is within 2^-8 max|v| of the exact one for the
+            # probabilities, and 2^-9 of itself for the store
+            tol = 1e-2 if lens[j] > 100 else 2.0 ** -7 * float(v.abs().max())
+            for out, l in (static, full):
+                assert float((out[j, 0, :, h].double() - ref).abs().max()) <= tol, (j, h)
+                assert float((l[j, 0, h].double() - lse).abs().max()) <= 2e-3, (j, h)
