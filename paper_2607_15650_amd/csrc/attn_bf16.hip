@@ -714,8 +714,18 @@ struct AsmCfg {
   static constexpr int TILEB = BN * ROWB;
   static constexpr int LW = TILEB / 1024 / NW;   // 1 KiB loads per wave per tile
   static constexpr int RING = 8 * TILEB;      // K ring (4 tiles), then V ring (4 tiles)
-  static constexpr size_t LDS_BYTES = RING + 16;
+  static constexpr int QSTAGE = QB * 32 * ROWB;     // a wave's query rows
+  // the ring, the redo flag and claimed unit, and the fourth wave's query rows
+  static constexpr int EXTRA = RING + 1024;
+  static constexpr size_t LDS_BYTES = EXTRA + QSTAGE;
   static_assert(QB * 32 * ROWB * NW <= RING, "output staging inside the ring");
+  static_assert(QSTAGE == TILEB, "a wave's query rows take one ring slot");
+  // Where a wave's query rows are staged: ring slots that no tile loaded
+  // before the first barrier goes to (K slot 3, V slots 2 and 3), then past
+  // the ring.
+  static constexpr __device__ int qstage(int wave) {
+    return wave == 0 ? 3 * TILEB : wave == 1 ? 6 * TILEB : wave == 2 ? 7 * TILEB : EXTRA;
+  }
 };
 
 // Bound on a lane's row sum below which the fast key loop's result is the
@@ -822,6 +832,7 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_asm_kernel(const AttnArgs a)
     const uint32_t kvl = (uint32_t)kv_len;
     const uint32_t wlds = __builtin_amdgcn_readfirstlane(smem_lds + (uint32_t)wave * (LW * 1024u));
     const uint32_t tileb = __builtin_amdgcn_readfirstlane(row_bytes * BN);
+    const uint32_t qstage = __builtin_amdgcn_readfirstlane((uint32_t)C::qstage(wave));
     // Two forms of the key loop.  The fast one takes the running maximum m
     // from tile 0 and keeps it; the checked one tests every tile and raises
     // m (slow path) where a lane's tile sum passes 2^40 or is not a number.
@@ -838,14 +849,19 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_asm_kernel(const AttnArgs a)
       const __bf16* vp = (const __bf16*)a.v + ((int64_t)b * a.S + kv0) * HD + (int64_t)h * D;
       u32x4 kd = raw_buffer_desc(kp, nrec);
       u32x4 vd = raw_buffer_desc(vp, nrec);
-      // the lane's Q rows (rows past q_len clamped: computed, never stored),
-      // advanced to dims 8g..8g+7
-      uint64_t qptr0, qptr1;
+      // the wave's Q rows into LDS, whole rows per 1 KiB load, units swizzled
+      // by row like a K tile's (rows past q_len clamped: computed, never
+      // stored); the block waits for them
       {
-        const __bf16* qb0 = (const __bf16*)a.q + ((int64_t)b * a.q_len + min(row0 + lr, a.q_len - 1)) * HD + (int64_t)h * D + 8 * g;
-        const __bf16* qb1 = (const __bf16*)a.q + ((int64_t)b * a.q_len + min(row0 + 32 + lr, a.q_len - 1)) * HD + (int64_t)h * D + 8 * g;
-        qptr0 = (uint64_t)(uintptr_t)qb0;
-        qptr1 = (uint64_t)(uintptr_t)qb1;
+        const int64_t rb0 = min(row0, a.q_len - 1);
+        const __bf16* base = (const __bf16*)a.q + ((int64_t)b * a.q_len + rb0) * HD + (int64_t)h * D;
+        const int last = (int)min((int64_t)(QB * 32 - 1), a.q_len - 1 - rb0);
+#pragma unroll
+        for (int i = 0; i < C::QSTAGE / 1024; ++i) {
+          const int row = i * C::ROWS_PER_LOAD + ld_row;
+          lds_dma16(base, (uint32_t)min(row, last) * row_bytes + (uint32_t)((ld_unit ^ swz_k<D>(row)) * 16),
+                    smem_lds + qstage + (uint32_t)(i * 1024));
+        }
       }
       if constexpr (D == 128) {
 #define DITANGO_D128_CALL(BODY)                                                                                       \
@@ -853,13 +869,13 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_asm_kernel(const AttnArgs a)
                : "={a[0:15]}"(o[0][0]), "={a[16:31]}"(o[0][1]), "={a[32:47]}"(o[0][2]), "={a[48:63]}"(o[0][3]),      \
                  "={a[64:79]}"(o[1][0]), "={a[80:95]}"(o[1][1]), "={a[96:111]}"(o[1][2]), "={a[112:127]}"(o[1][3]),   \
                  "={v230}"(m[0]), "={v231}"(m[1]), "={v232}"(l[0]), "={v233}"(l[1]),                                  \
-                 "+{s[48:51]}"(kd), "+{s[52:55]}"(vd), "+{v[64:65]}"(qptr0), "+{v[66:67]}"(qptr1)                     \
+                 "+{s[48:51]}"(kd), "+{s[52:55]}"(vd)                                                                 \
                : "{v234}"(kaddr[0]), "{v235}"(kaddr[1]), "{v236}"(kaddr[2]), "{v237}"(kaddr[3]),                      \
                  "{v238}"(kaddr[4]), "{v239}"(kaddr[5]), "{v240}"(kaddr[6]), "{v241}"(kaddr[7]),                      \
                  "{v242}"(vaddr[0]), "{v243}"(vaddr[1]), "{v244}"(vaddr[2]), "{v245}"(vaddr[3]),                      \
                  "{v246}"(dmak[0]), "{v247}"(dmak[1]), "{v248}"(dmak[2]), "{v249}"(dmak[3]),                          \
                  "{v250}"(dmav[0]), "{v251}"(dmav[1]), "{v252}"(dmav[2]), "{v253}"(dmav[3]),                          \
-                 "{s40}"(sl2), "{s41}"(ntiles), "{s42}"(kvl), "{s44}"(wlds), "{s45}"(tileb)             \
+                 "{s40}"(sl2), "{s41}"(ntiles), "{s42}"(kvl), "{s44}"(wlds), "{s45}"(tileb), "{s46}"(qstage) \
                : DITANGO_D128_LOOP_CLOBBERS)
         if (pass == 0) {
           DITANGO_D128_CALL(DITANGO_D128_FAST_ASM);
@@ -872,11 +888,11 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_asm_kernel(const AttnArgs a)
   asm volatile(BODY                                                                                                   \
                : "={a[0:15]}"(o[0][0]), "={a[16:31]}"(o[0][1]), "={a[32:47]}"(o[1][0]), "={a[48:63]}"(o[1][1]),      \
                  "={v230}"(m[0]), "={v231}"(m[1]), "={v232}"(l[0]), "={v233}"(l[1]),                                  \
-                 "+{s[48:51]}"(kd), "+{s[52:55]}"(vd), "+{v[64:65]}"(qptr0), "+{v[66:67]}"(qptr1)                     \
+                 "+{s[48:51]}"(kd), "+{s[52:55]}"(vd)                                                                 \
                : "{v234}"(kaddr[0]), "{v235}"(kaddr[1]), "{v236}"(kaddr[2]), "{v237}"(kaddr[3]),                      \
                  "{v238}"(vaddr[0]), "{v239}"(vaddr[1]), "{v240}"(dmak[0]), "{v241}"(dmak[1]),                        \
                  "{v242}"(dmav[0]), "{v243}"(dmav[1]),                                                                \
-                 "{s40}"(sl2), "{s41}"(ntiles), "{s42}"(kvl), "{s44}"(wlds), "{s45}"(tileb)             \
+                 "{s40}"(sl2), "{s41}"(ntiles), "{s42}"(kvl), "{s44}"(wlds), "{s45}"(tileb), "{s46}"(qstage) \
                : DITANGO_D64_LOOP_CLOBBERS)
         if (pass == 0) {
           DITANGO_D64_CALL(DITANGO_D64_FAST_ASM);

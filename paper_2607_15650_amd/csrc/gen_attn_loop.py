@@ -98,7 +98,7 @@ def DMAV(j):
     return 234 + KS + DB + LW + j
 
 
-QPTR = 64                      # v[64:67]: the lane's Q row addresses, one per query block
+QADDR = 64                     # v64-v71: LDS addresses of the lane's Q fragments (prologue only)
 
 
 def O(qb, db):                 # AGPR accumulators of O^T
@@ -110,7 +110,7 @@ def Q(qb, s):                  # AGPR Q^T fragments
 
 
 # scalar registers: inputs pinned by the caller, then scratch
-S_SL2, S_NT, S_KVLEN, S_WLDS, S_TILEB = 40, 41, 42, 44, 45
+S_SL2, S_NT, S_KVLEN, S_WLDS, S_TILEB, S_QSTAGE = 40, 41, 42, 44, 45, 46
 S_KD, S_VD = 48, 52            # buffer descriptors (4 each)
 S_I, S_TMP, S_BIG, S_MASKAT, S_RET, S_CMP, S_NTM1, S_LIM = 56, 57, 58, 59, 60, 62, 64, 65
 SCRATCH_SGPRS = list(range(56, 66))
@@ -521,6 +521,9 @@ def tile0_max():
 def prologue(g):
     L_ = g.lines
     L_ += ["s_nop 4"]
+    # K_0, K_1, V_0, K_2, V_1 on their way, then everything that needs none
+    for desc, ring, t in ((S_KD, KRING, 0), (S_KD, KRING, 1), (S_VD, VRING, 0), (S_KD, KRING, 2), (S_VD, VRING, 1)):
+        L_ += sum(dma_tile(desc, ring, t), []) + desc_advance(desc)
     for qb in range(2):
         L_ += [f"v_mov_b32 {v(M(qb))}, 0xff800000", f"v_mov_b32 {v(L(qb))}, 0"]
     L_ += [f"v_accvgpr_write_b32 {a_(r)}, 0" for r in range(32 * DB)]
@@ -531,21 +534,30 @@ def prologue(g):
            f"s_and_b32 {s_(S_TMP)}, {s_(S_KVLEN)}, 63",
            f"s_cmp_eq_u32 {s_(S_TMP)}, 0",
            f"s_cselect_b32 {s_(S_MASKAT)}, -1, {s_(S_MASKAT)}"]
-    # K_0, K_1, V_0, K_2, V_1
-    for desc, ring, t in ((S_KD, KRING, 0), (S_KD, KRING, 1), (S_VD, VRING, 0), (S_KD, KRING, 2), (S_VD, VRING, 1)):
-        L_ += sum(dma_tile(desc, ring, t), []) + desc_advance(desc)
-    # Q^T fragments: 16 bytes per lane per (query block, k-step), into v0-v63
+    # the wave's Q rows (loaded into its staging space in LDS by the code
+    # before the block) and K_0 have landed: only the later tiles may be in
+    # flight.  Q^T fragments come from the staging space, laid out and
+    # swizzled like a K tile's rows.
+    L_ += [f"s_waitcnt vmcnt({4 * LW})"]
+    for s in range(KS):
+        L_.append(f"v_add_u32 {v(QADDR + s)}, {s_(S_QSTAGE)}, {v(KADDR(s))}")
     for qb in range(2):
         for s in range(KS):
-            L_.append(f"global_load_dwordx4 {v(32 * qb + 4 * s, 4)}, {v(QPTR + 2 * qb, 2)}, off offset:{32 * s}")
-    L_ += ["s_waitcnt vmcnt(0)"]
+            L_.append(f"ds_read_b128 {v(32 * qb + 4 * s, 4)}, {v(QADDR + s)} offset:{qb * 32 * ROWB}")
+    L_ += ["s_waitcnt lgkmcnt(0)"]
     for qb in range(2):
         for s in range(KS):
             for j in range(4):
                 L_.append(f"v_accvgpr_write_b32 {a_(Q(qb, s) + j)}, {v(32 * qb + 4 * s + j)}")
+    # every wave's part of K_0 has landed, and every wave has read its Q rows
+    # (the staging space is ring space that iteration 0 loads into)
     L_ += ["s_nop 2", "s_barrier"]
-    # scores of tile 0, with the reads of iteration 0's first steps
-    L_ += stream(qk_steps(0, 0), qk_steps(1, 1)[:LA], {}, {}, 0)
+    # scores of tile 0 while K_1 and V_0 arrive
+    L_ += stream(qk_steps(0, 0), [], {}, {}, 0)
+    L_ += [f"s_waitcnt vmcnt({2 * LW})", "s_barrier"]
+    # the reads of iteration 0's first steps
+    for st in qk_steps(1, 1)[:LA]:
+        L_ += st.reads
     # a single tile that is partial: mask it
     L_ += [f"s_cmp_eq_u32 {s_(S_NT)}, 1"]
     L_ += g.out_of_line("s_cbranch_scc1", [
@@ -719,10 +731,9 @@ def write(d):
             f.write("\\n\\t".join(lines))
             f.write("\\n\"\n")
         # registers the block writes besides its outputs: scores,
-        # probabilities, fragments, temporaries, tile sums (the Q address
-        # registers v64-v67 are in/out operands), the Q^T AGPRs, scalar
-        # scratch
-        clob = [f'"v{i}"' for i in range(0, 64)] + [f'"v{i}"' for i in range(68, 230)]
+        # probabilities, fragments, temporaries, tile sums, the Q^T AGPRs,
+        # scalar scratch
+        clob = [f'"v{i}"' for i in range(0, 230)]
         clob += [f'"a{i}"' for i in range(128, Q(1, KS - 1) + 4)]
         clob += [f'"s{i}"' for i in SCRATCH_SGPRS]
         clob += ['"m0"', '"vcc"', '"scc"', '"memory"']
