@@ -148,6 +148,21 @@ ditango_status ditango_attn_partition_states_ws(
     void* workspace, size_t workspace_bytes, void* stream);
 
 /*
+ * The same for a block of rows of a longer query tensor, read in place: q is
+ * [B][q_rows][H][D], and the query block is rows [q_begin, q_begin + q_len)
+ * of every batch (a context-parallel rank's block of the whole sequence's
+ * queries).  ditango_attn_partition_states_ws(...) is this call with q_rows =
+ * q_len and q_begin = 0.  DITANGO_ERR_INVALID for a block outside the rows.
+ */
+ditango_status ditango_attn_block_states(
+    const void* q, int64_t q_rows, int64_t q_begin,
+    const void* k, const void* v, ditango_dtype dt,
+    int B, int H, int D, int64_t q_len,
+    const int64_t* kv_offsets, int P, const uint8_t* select, float scale,
+    void* out_states, ditango_dtype state_dt, float* lse_states,
+    void* workspace, size_t workspace_bytes, void* stream);
+
+/*
  * Workspace bytes ditango_attn_partition_states_ws uses for this launch on
  * the current HIP device: 256 for the queue counters, plus the partial
  * states of the tail split when a split shortens the last round (the

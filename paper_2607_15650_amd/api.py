@@ -63,20 +63,12 @@ def attn_workspace_bytes(dtype: torch.dtype, B: int, H: int, D: int, q_len: int,
     return int(_lib.lib().ditango_attn_workspace_bytes(_DT[dtype], B, H, D, q_len, offs, P, sel))
 
 
-def attn_partition_states(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor,
-                          offsets: Sequence[int], select: Sequence[int], scale: float,
-                          out_states: torch.Tensor, lse_states: torch.Tensor,
-                          workspace: Optional[torch.Tensor] = None) -> None:
-    """Fresh states of the selected partitions into their slots
-    (ditango_attn_partition_states).  Unselected slots are left untouched.
-    ``out_states`` is in the input dtype, or float32 for bf16 inputs
-    (ditango_attn_partition_states_ex: states at full precision).  With a
-    ``workspace`` (uint8, 256-byte aligned; ditango_attn_partition_states_ws)
-    the last tasks are claimed from queue counters in its first 256 bytes,
-    and with attn_workspace_bytes(...) bytes the last round is split over
-    key ranges as well."""
+def _attn_checks(q, q_len, k, v, offsets, select, out_states, lse_states, workspace):
+    """Checks of the attention calls; q_len None: all rows of q.  Returns the
+    sizes (B, q_len, H, D, P)."""
     _dev(q, k, v, out_states, lse_states, workspace)
-    B, q_len, H, D = q.shape
+    B, rows, H, D = q.shape
+    q_len = rows if q_len is None else q_len
     P = len(offsets) - 1
     if len(select) != P:
         raise ValueError("select must have one entry per partition")
@@ -92,6 +84,22 @@ def attn_partition_states(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor,
         raise ValueError("lse_states must be float32 [P, B, H, q_len]")
     if k.dtype != q.dtype or v.dtype != q.dtype:
         raise ValueError("q, k, v must share a dtype")
+    return B, q_len, H, D, P
+
+
+def attn_partition_states(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor,
+                          offsets: Sequence[int], select: Sequence[int], scale: float,
+                          out_states: torch.Tensor, lse_states: torch.Tensor,
+                          workspace: Optional[torch.Tensor] = None) -> None:
+    """Fresh states of the selected partitions into their slots
+    (ditango_attn_partition_states).  Unselected slots are left untouched.
+    ``out_states`` is in the input dtype, or float32 for bf16 inputs
+    (ditango_attn_partition_states_ex: states at full precision).  With a
+    ``workspace`` (uint8, 256-byte aligned; ditango_attn_partition_states_ws)
+    the last tasks are claimed from queue counters in its first 256 bytes,
+    and with attn_workspace_bytes(...) bytes the last round is split over
+    key ranges as well."""
+    B, q_len, H, D, P = _attn_checks(q, None, k, v, offsets, select, out_states, lse_states, workspace)
     offs = (ctypes.c_int64 * (P + 1))(*[int(x) for x in offsets])
     sel = (ctypes.c_uint8 * P)(*[1 if s else 0 for s in select])
     if workspace is not None:
@@ -111,6 +119,27 @@ def attn_partition_states(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor,
             offs, P, sel, float(scale), out_states.data_ptr(), _dtype(out_states), lse_states.data_ptr(),
             _stream())
         _lib.check("ditango_attn_partition_states_ex", st)
+
+
+def attn_block_states(q_all: torch.Tensor, q_begin: int, q_len: int, k: torch.Tensor, v: torch.Tensor,
+                      offsets: Sequence[int], select: Sequence[int], scale: float,
+                      out_states: torch.Tensor, lse_states: torch.Tensor,
+                      workspace: Optional[torch.Tensor] = None) -> None:
+    """attn_partition_states for the query block of rows [q_begin, q_begin +
+    q_len) of every batch of ``q_all`` [B, rows, H, D], read in place
+    (ditango_attn_block_states)."""
+    B, _, H, D, P = _attn_checks(q_all, q_len, k, v, offsets, select, out_states, lse_states, workspace)
+    rows = q_all.shape[1]
+    if q_begin < 0 or q_begin + q_len > rows:
+        raise ValueError("the query block must lie inside q_all")
+    offs = (ctypes.c_int64 * (P + 1))(*[int(x) for x in offsets])
+    sel = (ctypes.c_uint8 * P)(*[1 if s else 0 for s in select])
+    ws, n = (workspace.data_ptr(), workspace.numel() * workspace.element_size()) if workspace is not None else (None, 0)
+    st = _lib.lib().ditango_attn_block_states(
+        q_all.data_ptr(), rows, int(q_begin), k.data_ptr(), v.data_ptr(), _dtype(q_all), B, H, D, q_len,
+        offs, P, sel, float(scale), out_states.data_ptr(), _dtype(out_states), lse_states.data_ptr(),
+        ws, n, _stream())
+    _lib.check("ditango_attn_block_states", st)
 
 
 def merge_states(out_states: torch.Tensor, lse_states: torch.Tensor, out: torch.Tensor,

@@ -110,9 +110,11 @@ class ErrorModelSelectiveAttention:
         self.snapbuf[slot].copy_(self.cache[self.q])
         self.snap[t] = slot
 
-    def _attn(self, q, k, v, sel, states, lses):
-        ws = self._attn_ws.get(q.dtype, q.shape[0], q.shape[2], q.shape[3], q.shape[1], self.offsets, sel)
-        api.attn_partition_states(q, k, v, self.offsets, sel, self.scale, states, lses, ws)
+    def _attn(self, qb, k, v, sel, states, lses):
+        """qb: (query tensor, the block's first row in it)"""
+        q, q0 = qb
+        ws = self._attn_ws.get(q.dtype, q.shape[0], q.shape[2], q.shape[3], self.L, self.offsets, sel)
+        api.attn_block_states(q, q0, self.L, k, v, self.offsets, sel, self.scale, states, lses, ws)
 
     def _compose_group(self, states, lses, grp):
         if grp[1] - grp[0] > 1:
@@ -125,7 +127,7 @@ class ErrorModelSelectiveAttention:
         when the model is evaluated, ``measured`` (group -> the error its cached
         state actually carries) at every step after the first."""
         a, e = self.offsets[self.q], self.offsets[self.q + 1]
-        qb = q_all[:, a:e].contiguous()
+        qb = (q_all, a) if q_all.is_contiguous() else (q_all[:, a:e].contiguous(), 0)
         loc = [0] * self.P
         loc[self.q] = 1
         self._attn(qb, k, v, loc, self.cache, self.cache_lse)          # local partition first

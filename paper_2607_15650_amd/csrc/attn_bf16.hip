@@ -351,7 +351,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void attn_bf16_kernel(const AttnArgs 
   if (kv_len > 0) {
     // rows past q_len are clamped to the last row: computed, never stored
     const int64_t rb0 = min(row0, a.q_len - 1);
-    const __bf16* base = qg + ((int64_t)b * a.q_len + rb0) * HD + (int64_t)h * D;
+    const __bf16* base = qg + (int64_t)b * a.q_stride + rb0 * HD + (int64_t)h * D;
     const uint32_t dst = smem_lds + (uint32_t)(kStage + wave * kStageWave);
 #pragma unroll
     for (int i = 0; i < kStageWave / 1024; ++i) {
@@ -854,7 +854,7 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_asm_kernel(const AttnArgs a)
       // stored); the block waits for them
       {
         const int64_t rb0 = min(row0, a.q_len - 1);
-        const __bf16* base = (const __bf16*)a.q + ((int64_t)b * a.q_len + rb0) * HD + (int64_t)h * D;
+        const __bf16* base = (const __bf16*)a.q + (int64_t)b * a.q_stride + rb0 * HD + (int64_t)h * D;
         const int last = (int)min((int64_t)(QB * 32 - 1), a.q_len - 1 - rb0);
 #pragma unroll
         for (int i = 0; i < C::QSTAGE / 1024; ++i) {

@@ -414,7 +414,7 @@ __global__ __launch_bounds__(C::NT, C::WPE) void attn_f32_kernel(const AttnArgs 
   const int rl = (C::KW == 1 ? wave * 32 : 0) + lr;          // row within the workgroup's tile
   const int64_t row = (int64_t)qt * C::BM + rl;
   const bool row_ok = row < a.q_len;
-  const float* qrow = (const float*)a.q + ((int64_t)b * a.q_len + (row_ok ? row : 0)) * HD + (int64_t)h * D;
+  const float* qrow = (const float*)a.q + (int64_t)b * a.q_stride + (row_ok ? row : 0) * HD + (int64_t)h * D;
 
   // this wave's key tiles, and its tile space in LDS
   const int tiles = (kv_len + C::BN - 1) / C::BN;

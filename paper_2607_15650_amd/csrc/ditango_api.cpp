@@ -67,6 +67,7 @@ ditango_status attn_args(const void* q, const void* k, const void* v, ditango_dt
   a->out_states = const_cast<void*>(out_states);
   a->lse_states = const_cast<float*>(lse_states);
   a->q_len = q_len;
+  a->q_stride = q_len * H * D;
   a->S = kv_offsets[P];
   a->B = B;
   a->H = H;
@@ -93,12 +94,26 @@ ditango_status ditango_attn_partition_states_ws(
     const int64_t* kv_offsets, int P, const uint8_t* select, float scale,
     void* out_states, ditango_dtype state_dt, float* lse_states,
     void* workspace, size_t workspace_bytes, void* stream) {
+  return ditango_attn_block_states(q, q_len, 0, k, v, dt, B, H, D, q_len, kv_offsets, P, select, scale, out_states,
+                                   state_dt, lse_states, workspace, workspace_bytes, stream);
+}
+
+ditango_status ditango_attn_block_states(
+    const void* q, int64_t q_rows, int64_t q_begin,
+    const void* k, const void* v, ditango_dtype dt,
+    int B, int H, int D, int64_t q_len,
+    const int64_t* kv_offsets, int P, const uint8_t* select, float scale,
+    void* out_states, ditango_dtype state_dt, float* lse_states,
+    void* workspace, size_t workspace_bytes, void* stream) {
   AttnArgs a;
   const ditango_status st = attn_args(q, k, v, dt, B, H, D, q_len, kv_offsets, P, select, scale, out_states,
                                       state_dt, lse_states, &a);
   if (st != DITANGO_OK) return st;
+  if (q_begin < 0 || q_rows < q_len || q_begin > q_rows - q_len) return DITANGO_ERR_INVALID;
   if (workspace != nullptr && ((uintptr_t)workspace & 255u) != 0) return DITANGO_ERR_INVALID;
   if (a.n_sel == 0) return DITANGO_OK;
+  a.q = (const char*)q + q_begin * H * D * (dt == DITANGO_F32 ? 4 : 2);
+  a.q_stride = q_rows * H * D;
   hipStream_t s = (hipStream_t)stream;
   if (dt == DITANGO_BF16)
     return from_hip(launch_attn_bf16_ws(a, D, state_dt == DITANGO_F32, workspace_bytes > 0 ? workspace : nullptr,

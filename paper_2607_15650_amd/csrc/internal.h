@@ -13,12 +13,13 @@ constexpr int kMaxParts = DITANGO_MAX_PARTITIONS;
 
 // One launch of the fresh-state kernel covers every selected partition.
 struct AttnArgs {
-  const void* q;            // [B][q_len][H][D]
+  const void* q;            // [B][q_len][H][D], batches q_stride elements apart
   const void* k;            // [B][S][H][D]
   const void* v;            // [B][S][H][D]
   void* out_states;         // [P][B][q_len][H][D], state dtype
   float* lse_states;        // [P][B][H][q_len]
   int64_t q_len;
+  int64_t q_stride;
   int64_t S;
   int B, H;
   int n_sel;                // number of selected partitions

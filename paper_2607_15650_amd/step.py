@@ -65,11 +65,12 @@ class SelectiveAttention:
         """
         c = self.cache(qb)
         a, e = self.offsets[qb], self.offsets[qb + 1]
-        q = q_all[:, a:e]
-        if not q.is_contiguous():
-            q = q.contiguous()
-        ws = self._attn_ws.get(q.dtype, self.B, self.H, self.D, e - a, self.offsets, select)
-        api.attn_partition_states(q, k, v, self.offsets, select, self.scale, c.out, c.lse, ws)
+        ws = self._attn_ws.get(q_all.dtype, self.B, self.H, self.D, e - a, self.offsets, select)
+        if q_all.is_contiguous():
+            api.attn_block_states(q_all, a, e - a, k, v, self.offsets, select, self.scale, c.out, c.lse, ws)
+        else:
+            q = q_all[:, a:e].contiguous()
+            api.attn_partition_states(q, k, v, self.offsets, select, self.scale, c.out, c.lse, ws)
         for j, s in enumerate(select):
             if s:
                 c.computed_at[j] = step

@@ -1,4 +1,5 @@
-"""Argument validation of ditango_compose, on the host (nothing is launched)."""
+"""Argument validation of ditango_compose and ditango_attn_block_states, on the
+host (nothing is launched)."""
 import ctypes
 
 import pytest
@@ -34,3 +35,18 @@ def test_compose_is_not_in_place(compose):
     assert call(compose, out=FAKE + 2 * slot) == 1
     assert call(compose, lse_out=FAKE + 3 * rows) == 1
     assert call(compose, slots=[1, 2], n=2, out=FAKE + 2 * slot) == 1
+
+
+def test_attn_block_validation():
+    from paper_2607_15650_amd import _lib
+    f = _lib.lib().ditango_attn_block_states
+    o = (ctypes.c_int64 * 3)(0, 5, 10)
+
+    def block(rows, begin, q_len=10, q=FAKE, sel=(0, 0), D=64, ws=None):
+        s = (ctypes.c_uint8 * 2)(*sel)
+        return f(q, rows, begin, FAKE, FAKE, 1, 1, 2, D, q_len, o, 2, s, 0.1, FAKE, 1, FAKE, ws, 0, None)
+
+    assert block(10, 0) == 0 and block(30, 20) == 0             # nothing selected: nothing launched
+    assert block(9, 0) == 1 and block(30, 21) == 1 and block(30, -1) == 1
+    assert block(30, 1 << 62) == 1 and block(30, 0, q=None) == 1 and block(30, 0, D=96) == 2
+    assert block(30, 0, ws=FAKE + 64) == 1

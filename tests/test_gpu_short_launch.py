@@ -57,3 +57,41 @@ def test_launches_match_static_and_float64(D, H, q_len, lens):
             for out, l in (static, full):
                 assert float((out[j, 0, :, h].double() - ref).abs().max()) <= tol, (j, h)
                 assert float((l[j, 0, h].double() - lse).abs().max()) <= 2e-3, (j, h)
+
+
+@pytest.mark.parametrize("dtype,D,H", [("bf16", 64, 3), ("bf16", 128, 3), ("f32", 64, 3), ("f32", 128, 60)])
+@pytest.mark.parametrize("q_begin,q_len", [(0, 257), (300, 257), (443, 257), (699, 1)])
+def test_query_block_read_in_place(dtype, D, H, q_begin, q_len):
+    """The block of a longer query tensor, batch of 2: bit for bit the launch
+    on a copy of its rows; blocks outside the rows are refused."""
+    import torch
+    from paper_2607_15650_amd import _lib, api
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    offs = [0, 200, 430]
+    g = torch.Generator(device="cuda").manual_seed(D)
+    q, k, v = (torch.randn((2, n, H, D), generator=g, device="cuda").to(dt) for n in (700, 430, 430))
+    got, ref = ([torch.full((2, 2, q_len, H, D), 9.0, dtype=dt, device="cuda"),
+                 torch.full((2, 2, H, q_len), 9.0, device="cuda")] for _ in range(2))
+    n = api.attn_workspace_bytes(dt, 2, H, D, q_len, offs, [1, 1])
+    ws = torch.empty(n, dtype=torch.uint8, device="cuda") if n else None
+    api.attn_block_states(q, q_begin, q_len, k, v, offs, [1, 1], D ** -0.5, *got, ws)
+    api.attn_partition_states(q[:, q_begin:q_begin + q_len].contiguous(), k, v, offs, [1, 1], D ** -0.5, *ref, ws)
+    assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1])
+    for bad in (-1, 700 - q_len + 1):
+        with pytest.raises(ValueError):
+            api.attn_block_states(q, bad, q_len, k, v, offs, [1, 1], D ** -0.5, *got, ws)
+
+
+def test_step_takes_a_strided_query_tensor():
+    """Query tensors that are not contiguous are copied, as before."""
+    import torch
+    from paper_2607_15650_amd.step import SelectiveAttention
+    g = torch.Generator(device="cuda").manual_seed(0)
+    q, k, v = (torch.randn((2, 600, 2, 64), generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    wide = torch.stack([q, q], dim=3)[:, :, :, 0]
+    assert not wide.is_contiguous()
+    res = []
+    for x in (q, wide):
+        sa = SelectiveAttention(2, 2, 64, [0, 200, 400, 600], 0.125)
+        res.append(sa.step(0, 1, x, k, v, [1, 1, 1]))
+    assert all(torch.equal(a, b) for a, b in zip(*res))
