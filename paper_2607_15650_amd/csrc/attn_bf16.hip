@@ -238,6 +238,15 @@ __device__ int claim_unit(const AttnArgs& a, int lane) {
   return -1;
 }
 
+// Partial OUT of the 32-row block that holds row `prow` of the split units'
+// rows: the block's accumulators as they lie in registers, [dim block][r4]
+// [lane][4] (lane 32g + r: row r, dims 32db + 8r4 + 4g ...), so that every
+// store of a unit is 1 KiB of consecutive bytes (row-major, its 64 lanes
+// wrote 16 bytes to each of 32 rows).
+template <int D> __device__ __forceinline__ float* part_block(const AttnArgs& a, int64_t prow) {
+  return a.part_out + (prow >> 5) * (32 * D);
+}
+
 template <int D, int QB, int NW, int BN, int NBUF, int WPE, bool SEQ, typename TS>
 __global__ __launch_bounds__(NW * 64, WPE) void attn_bf16_kernel(const AttnArgs a) {
   using C = Cfg<D, QB, NW, BN, NBUF>;
@@ -656,8 +665,8 @@ __global__ __launch_bounds__(NW * 64, WPE) void attn_bf16_kernel(const AttnArgs 
         }
         if (g == 0) a.lse_states[(((int64_t)slot * a.B + b) * a.H + h) * a.q_len + row] = lse;
       } else {
-        const int64_t rl = row - (int64_t)qt * C::BM;            // row within the query tile
-        float* dst = a.part_out + (pt * C::BM + rl) * D + 4 * g;
+        const int rl = wave * (QB * 32) + qb * 32 + lr;          // row within the query tile
+        float* dst = part_block<D>(a, pt * C::BM + rl) + lane * 4;
 #pragma unroll
         for (int db = 0; db < C::DB; ++db)
 #pragma unroll
@@ -665,7 +674,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void attn_bf16_kernel(const AttnArgs 
             f32x4 x;
 #pragma unroll
             for (int e = 0; e < 4; ++e) x[e] = o[qb][db][4 * r4 + e] * inv;
-            store4(dst + db * 32 + 8 * r4, x);
+            store4(dst + (4 * db + r4) * 256, x);
           }
         if (g == 0) a.part_lse[pt * C::BM + rl] = lse;
       }
@@ -962,8 +971,8 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_asm_kernel(const AttnArgs a)
         }
         if (g == 0) a.lse_states[(((int64_t)slot * a.B + b) * a.H + h) * a.q_len + row] = lse;
       } else {
-        const int64_t rl = row - (int64_t)qt * C::BM;
-        float* dst = a.part_out + (pt * C::BM + rl) * D + 4 * g;
+        const int rl = wave * (QB * 32) + qb * 32 + lr;  // row within the query tile
+        float* dst = part_block<D>(a, pt * C::BM + rl) + lane * 4;
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -971,7 +980,7 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_asm_kernel(const AttnArgs a)
             f32x4 x;
 #pragma unroll
             for (int e = 0; e < 4; ++e) x[e] = o[qb][db][4 * r4 + e] * inv;
-            store4(dst + db * 32 + 8 * r4, x);
+            store4(dst + (4 * db + r4) * 256, x);
           }
         if (g == 0) a.part_lse[pt * C::BM + rl] = lse;
       }
@@ -996,16 +1005,18 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_asm_kernel(const AttnArgs a)
 
 // Composes the split_f partial states of every split task (Eq. composition
 // over its key ranges) into the task's rows of its slot.  One thread per 8
-// elements of a row.
+// elements of a row; consecutive threads take consecutive rows of a 32-row
+// block, which is how the partial states lie (part_block).
 template <int D, int BM, typename TS>
 __global__ __launch_bounds__(256) void attn_split_fixup_kernel(const AttnArgs a) {
   constexpr int CPR = D / 8;
   const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (c >= (int64_t)a.n_split * BM * CPR) return;
-  const int ch = (int)(c % CPR);
-  const int64_t rr = c / CPR;
-  const int rl = (int)(rr % BM);
-  const int t = (int)(rr / BM);
+  const int lr = (int)(c & 31);
+  const int ch = (int)((c >> 5) % CPR);
+  const int64_t rb = (c >> 5) / CPR;
+  const int rl = (int)(rb % (BM / 32)) * 32 + lr;
+  const int t = (int)(rb / (BM / 32));
   int task = a.n_main + t;
   const int qt = task % a.q_tiles;
   task /= a.q_tiles;
@@ -1018,12 +1029,24 @@ __global__ __launch_bounds__(256) void attn_split_fixup_kernel(const AttnArgs a)
   const int f = a.split_f;
   const int64_t p0 = (int64_t)t * f;
   float lv[kMaxSplit];
-  float mx = -INFINITY;
+  f32x4 x0[kMaxSplit], x1[kMaxSplit];
 #pragma unroll
   for (int p = 0; p < kMaxSplit; ++p) {
-    lv[p] = p < f ? a.part_lse[(p0 + p) * BM + rl] : -INFINITY;
-    mx = fmaxf(mx, lv[p]);
+    lv[p] = -INFINITY;
+    if (p < f) lv[p] = a.part_lse[(p0 + p) * BM + rl];
   }
+#pragma unroll
+  for (int p = 0; p < kMaxSplit; ++p) {
+    x0[p] = x1[p] = f32x4{};
+    if (p < f) {
+      const float* src = part_block<D>(a, (p0 + p) * BM + rl) + ch * 256 + lr * 4;
+      x0[p] = *(const f32x4*)src;
+      x1[p] = *(const f32x4*)(src + 128);
+    }
+  }
+  float mx = -INFINITY;
+#pragma unroll
+  for (int p = 0; p < kMaxSplit; ++p) mx = fmaxf(mx, lv[p]);
   float tot = 0.f;
 #pragma unroll
   for (int p = 0; p < kMaxSplit; ++p) {
@@ -1035,10 +1058,9 @@ __global__ __launch_bounds__(256) void attn_split_fixup_kernel(const AttnArgs a)
 #pragma unroll
   for (int p = 0; p < kMaxSplit; ++p) {
     if (p < f) {
-      const float* src = a.part_out + ((p0 + p) * BM + rl) * D + ch * 8;
       const float w = lv[p] * inv;
-      acc0 += w * *(const f32x4*)src;
-      acc1 += w * *(const f32x4*)(src + 4);
+      acc0 += w * x0[p];
+      acc1 += w * x1[p];
     }
   }
   const int slot = a.slot[sel];

@@ -62,12 +62,17 @@ constexpr size_t kQueueBytes = 256;   // the queue counters, at the start of the
 // unsplit; split into f key ranges it is ceil(f * rem / slots) rounds of
 // ceil(tiles / f) + kSplitUnitCost (a split unit loads its queries again and
 // writes its partial state in float32), plus kFixupCost for the kernel that
-// composes the partials.  Returns the f in [2, kMaxSplit] with the lowest
-// estimate (the smallest on ties) when it is at least 3 % below the
-// unsplit one, else 1.  Launches with more than kMaxSplitRounds full rounds
-// before the last are not split: the workgroups' speeds differ by a few
-// percent, so after many rounds their finish times are spread over much of
-// a task and the queue counters hand the last tasks to the earliest
+// composes the partials (both higher, ...First, in a launch without a full
+// round before: nothing of the split's own time is hidden there, and the
+// compute units that stay idle unsplit let the busy ones clock up.  126 tasks
+// of 26 tiles split 2 ways ran 29.2 us at D=64 and 39.4 at D=128, whole 26.0
+// and 36.6; 96 of 32 tiles 28.8 either way; 140 of 63 tiles split 3 ways 83
+// at D=128, whole 76).  Returns the f in [2, kMaxSplit] with the lowest
+// estimate (the smallest on ties) when it is at least 3 % below the unsplit
+// one, else 1.  Launches with more than kMaxSplitRounds full rounds before
+// the last are not split: the workgroups' speeds differ by a few percent, so
+// after many rounds their finish times are spread over much of a task and
+// the queue counters hand the last tasks to the earliest
 // finishers (measured: a 4,440-task launch on 256 CUs ran 0.4-1.2 % faster
 // balanced and unsplit than balanced and split 5 or 8 ways, on three
 // cards; 1,480 and 8,880 tasks alike; a 216-task single round of 22-tile
@@ -75,6 +80,8 @@ constexpr size_t kQueueBytes = 256;   // the queue counters, at the start of the
 constexpr int kMainUnitCost = 1;
 constexpr int kSplitUnitCost = 4;
 constexpr int kFixupCost = 3;
+constexpr int kSplitUnitCostFirst = 5;
+constexpr int kFixupCostFirst = 12;
 constexpr int kMaxSplitRounds = 4;
 
 inline int plan_tail_split(int64_t tasks, int64_t slots, int64_t tiles) {
@@ -82,12 +89,15 @@ inline int plan_tail_split(int64_t tasks, int64_t slots, int64_t tiles) {
   if (tasks / slots > kMaxSplitRounds) return 1;
   const int64_t rem = tasks % slots;
   if (rem == 0) return 1;
+  const bool first = tasks < slots;
+  const int unit = first ? kSplitUnitCostFirst : kSplitUnitCost;
+  const int fixup = first ? kFixupCostFirst : kFixupCost;
   const double unsplit = (double)(tiles + kMainUnitCost);
   int best = 1;
   double best_t = unsplit;
   for (int f = 2; f <= kMaxSplit; ++f) {
     const int64_t rounds = (f * rem + slots - 1) / slots;
-    const double t = (double)(rounds * ((tiles + f - 1) / f + kSplitUnitCost) + kFixupCost);
+    const double t = (double)(rounds * ((tiles + f - 1) / f + unit) + fixup);
     if (t < best_t - 1e-9) {
       best_t = t;
       best = f;
