@@ -198,22 +198,24 @@ ditango_status ditango_merge_states(
     int B, int H, int D, int64_t q_len,
     void* out, ditango_dtype out_dt, float* lse_out, void* stream);
 
-/* Device workspace of ditango_compose. */
-#define DITANGO_COMPOSE_WORKSPACE_BYTES 1024u
+/*
+ * Bytes of device workspace ditango_compose needs for these sizes.
+ */
+size_t ditango_compose_workspace_bytes(int B, int H, int64_t q_len, int n_slots);
 
 /*
  * ditango_merge_states and the listed slots' mean contribution weights
  * (Sec. 4.1.2, Eq. lse_weight) in one launch:
  *     w_part[i] = mean over all B*H*q_len rows of exp(LSE_slots[i] - LSE).
- * The sums over the rows do not depend on their order (integers of 2^-32):
- * bitwise identical from run to run.  At most 2^31 - 1 rows
- * (DITANGO_ERR_UNSUPPORTED beyond).
+ * Reduced in the order of ditango_contrib: the same bits as ditango_contrib
+ * over those slots' LSEs, on every run.
  *
  *   w_part     device, [n_slots] float32 (n_slots = P when slots is NULL).
- *   workspace  device, DITANGO_COMPOSE_WORKSPACE_BYTES, 256-byte aligned: sums
- *              and a counter.  The caller zeroes it once, after allocating it;
- *              every call leaves it zero for the next, whatever its sizes.
- *              Calls that overlap on one workspace race.
+ *   workspace  device, ditango_compose_workspace_bytes(...) bytes, 256-byte
+ *              aligned.  Its first 256 bytes hold a counter, which the caller
+ *              zeroes once, after allocating it; every call leaves it zero for
+ *              the next, of any size the workspace holds.  Calls that overlap
+ *              on one workspace race.
  * The other arguments are those of ditango_merge_states, except that `out` /
  * `lse_out` may not be a listed slot (DITANGO_ERR_INVALID).
  */

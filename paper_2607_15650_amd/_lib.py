@@ -17,7 +17,6 @@ OK, ERR_INVALID, ERR_UNSUPPORTED, ERR_HIP = 0, 1, 2, 3
 F32, BF16 = 0, 1
 MAX_PARTITIONS = 64
 CONTRIB_SCRATCH_BYTES = 1 << 20
-COMPOSE_WORKSPACE_BYTES = 1024
 
 # Every symbol include/ditango.h declares, with (restype, argtypes).
 _c = ctypes
@@ -50,6 +49,7 @@ SIGNATURES = {
         _c.c_int, _c.POINTER(_c.c_int32), _c.c_int,
         _c.c_int, _c.c_int, _c.c_int, _c.c_int64,
         _c.c_void_p, _c.c_int, _c.c_void_p, _c.c_void_p]),
+    "ditango_compose_workspace_bytes": (_c.c_size_t, [_c.c_int, _c.c_int, _c.c_int64, _c.c_int]),
     "ditango_compose": (_c.c_int, [
         _c.c_void_p, _c.c_void_p, _c.c_int,
         _c.c_int, _c.POINTER(_c.c_int32), _c.c_int,

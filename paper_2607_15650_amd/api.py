@@ -166,10 +166,11 @@ def merge_states(out_states: torch.Tensor, lse_states: torch.Tensor, out: torch.
     _lib.check("ditango_merge_states", st)
 
 
-def compose_workspace(device="cuda") -> torch.Tensor:
-    """A zeroed workspace for ``compose``; it serves any number of calls, of
-    any sizes, that do not overlap."""
-    return torch.zeros(_lib.COMPOSE_WORKSPACE_BYTES, dtype=torch.uint8, device=device)
+def compose_workspace(B: int, H: int, q_len: int, n_slots: int, device="cuda") -> torch.Tensor:
+    """A workspace for ``compose`` of these sizes, its counter zeroed; it
+    serves any number of calls that do not overlap."""
+    return torch.zeros(int(_lib.lib().ditango_compose_workspace_bytes(B, H, q_len, n_slots)), dtype=torch.uint8,
+                       device=device)
 
 
 def compose(out_states: torch.Tensor, lse_states: torch.Tensor, out: torch.Tensor, lse_out: Optional[torch.Tensor],
@@ -192,8 +193,9 @@ def compose(out_states: torch.Tensor, lse_states: torch.Tensor, out: torch.Tenso
         sl = (ctypes.c_int32 * n)(*[int(s) for s in slots])
     if tuple(w_part.shape) != (n,) or w_part.dtype != torch.float32:
         raise ValueError("w_part must be float32 [n_slots]")
-    if workspace.numel() * workspace.element_size() < _lib.COMPOSE_WORKSPACE_BYTES:
-        raise ValueError(f"workspace too small: need {_lib.COMPOSE_WORKSPACE_BYTES} bytes")
+    need = int(_lib.lib().ditango_compose_workspace_bytes(B, H, q_len, n))
+    if workspace.numel() * workspace.element_size() < need:
+        raise ValueError(f"workspace too small: need {need} bytes")
     st = _lib.lib().ditango_compose(
         out_states.data_ptr(), lse_states.data_ptr(), _dtype(out_states), P, sl, n,
         B, H, D, q_len, out.data_ptr(), _dtype(out),

@@ -206,6 +206,11 @@ ditango_status ditango_merge_states(
   return from_hip(launch_merge(a, state_dt, out_dt, D, (hipStream_t)stream));
 }
 
+size_t ditango_compose_workspace_bytes(int B, int H, int64_t q_len, int n_slots) {
+  if (B < 1 || H < 1 || q_len < 1 || n_slots < 1) return 0;
+  return compose_ws_bytes((int64_t)B * H * q_len, n_slots);
+}
+
 ditango_status ditango_compose(
     const void* out_states, const float* lse_states, ditango_dtype state_dt,
     int P, const int32_t* slots, int n_slots,
@@ -224,12 +229,13 @@ ditango_status ditango_compose(
     if (out == (const char*)out_states + (size_t)a.slots[j] * slot_bytes) return DITANGO_ERR_INVALID;
     if (lse_out == lse_states + (size_t)a.slots[j] * a.rows) return DITANGO_ERR_INVALID;
   }
-  if (a.rows > 0x7fffffffLL) return DITANGO_ERR_UNSUPPORTED;
-  a.n_wblocks = compose_wblocks(a.rows, a.n, &a.w_iters);
+  const int64_t nb = contrib_blocks(a.rows);
+  if (nb > 0x7fffffffLL / 4) return DITANGO_ERR_UNSUPPORTED;
+  a.w_blocks = (int)nb;
+  a.n_wblocks = compose_wblocks(a.rows, &a.w_iters);
   a.w_part = w_part;
-  a.w_sum = (uint64_t*)workspace;
-  a.w_count = (int*)(a.w_sum + kMaxParts);
-  static_assert(kMaxParts * sizeof(uint64_t) + sizeof(int) <= DITANGO_COMPOSE_WORKSPACE_BYTES, "workspace");
+  a.w_count = (int*)workspace;
+  a.w_partial = (float*)((char*)workspace + kComposeCountBytes);
   return from_hip(launch_merge(a, state_dt, out_dt, D, (hipStream_t)stream));
 }
 

@@ -117,11 +117,13 @@ struct MergeArgs {
   int n;                    // number of listed slots
   int32_t slots[kMaxParts];
   // Weights of the listed slots in the same launch: the first n_wblocks
-  // workgroups (0: composition only) take w_iters rounds of rows each.
+  // workgroups (0: composition only) take w_iters of the units of the
+  // w_blocks row blocks each.
   int n_wblocks;
   int w_iters;
+  int w_blocks;
   float* w_part;            // [n]
-  uint64_t* w_sum;          // [n] sums in units of 2^-32; 0 before and after the launch
+  float* w_partial;         // workspace [units][n]
   int* w_count;             // finished weight workgroups; 0 before and after the launch
 };
 
@@ -154,9 +156,11 @@ constexpr int kNormChunksPerBlock = kNormThreads * 16;   // 8-element chunks per
 // array (the workspace holds one partial sum per workgroup and partition).
 int64_t contrib_blocks(int64_t n_rows);
 
-// Weight workgroups of a composition with weights over n_rows rows and n
-// slots, and the rounds of rows each takes.
-int compose_wblocks(int64_t n_rows, int n, int* iters);
+// Weight workgroups of a composition with weights over n_rows rows, the units
+// each takes, and the workspace's bytes for n slots.
+int compose_wblocks(int64_t n_rows, int* iters);
+size_t compose_ws_bytes(int64_t n_rows, int n);
+constexpr size_t kComposeCountBytes = 256;   // the counter, at the start of the workspace
 
 // bf16 inputs; states in bf16, or in float32 when state_f32
 hipError_t launch_attn_bf16(const AttnArgs& a, int D, bool state_f32, hipStream_t s);

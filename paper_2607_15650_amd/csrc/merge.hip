@@ -105,38 +105,42 @@ __device__ __forceinline__ float weight_of(float lj, float lo) {
   return lo != -INFINITY && lj != -INFINITY ? __builtin_amdgcn_exp2f((lj - lo) * kLog2e) : 0.f;
 }
 
-// rows of a lane whose loads are in flight together, by the slot bound
-constexpr int weight_rows(int nmax) { return nmax <= 8 ? 2 : 1; }
+// Row blocks of the mean weights: the sums over one block, and over the
+// blocks, are formed in the same order by the weight workgroups of a
+// composition and by the weight kernels on their own, so that both give the
+// same bits.
+constexpr int kContribThreads = 256;
+constexpr int kContribRowsPerThread = 2;
+constexpr int kContribRowsPerBlock = kContribThreads * kContribRowsPerThread;
+constexpr int kContribWaves = kContribThreads / 64;
 
 // One weight workgroup (one wave) of a composition with weights: mean weights
 // of the listed slots over all rows, in one launch with the composition.  The
 // wave composes its rows' log-sum-exps itself (the composed ones are being
-// written by other workgroups), sums each slot's weights over its rows in
-// float32 and adds the sums, in units of 2^-32, to 64-bit integers: integer
-// sums do not depend on their order, so the means are the same bits on every
-// run.  (A weight lies in [0, 1] and is 0 where a log-sum-exp is not finite,
-// so up to 2^31 rows cannot overflow.)  The wave that finds all others
-// finished writes the means and leaves sums and counter at zero for the next
-// launch.
+// written by other workgroups), forms the sums of w_iters units - a unit is
+// what one of the kContribWaves waves of a contrib_partial_kernel workgroup
+// takes - and publishes them; the wave that finds all others finished adds
+// them up as those workgroups and contrib_final_kernel do, and leaves the
+// counter at zero for the next launch.
 //
-// Sums and counter are touched with device-scope atomics only: the XCDs' L2
-// caches are not coherent with each other, and an atomic's result is in none
-// of them.  A wave's sums are added (vmcnt) before it counts itself finished.
+// The sums and the counter are read and written with device-scope atomics
+// only: the XCDs' L2 caches are not coherent with each other, and an atomic's
+// result is in none of them.  A wave's sums are complete (vmcnt) before it
+// counts itself finished.
 template <int NMAX>
 __device__ void weights_block(const MergeArgs& a) {
-  constexpr int R = weight_rows(NMAX);
+  constexpr int R = kContribRowsPerThread;
   const int lane = threadIdx.x;
   const int n = a.n;
   const int64_t n_rows = a.rows;
-  float acc[NMAX];
-#pragma unroll
-  for (int j = 0; j < NMAX; ++j) acc[j] = 0.f;
-  for (int it = 0; it < a.w_iters; ++it) {
-    const int64_t base = ((int64_t)blockIdx.x * a.w_iters + it) * (R * kMergeThreads) + lane;
+  const int units = a.w_blocks * kContribWaves;
+  const int u1 = min(((int)blockIdx.x + 1) * a.w_iters, units);
+  for (int u = blockIdx.x * a.w_iters; u < u1; ++u) {
+    const int64_t base = (int64_t)(u / kContribWaves) * kContribRowsPerBlock + (u % kContribWaves) * 64 + lane;
     float lv[R][NMAX];
 #pragma unroll
     for (int i = 0; i < R; ++i) {
-      const int64_t r = base + i * kMergeThreads;
+      const int64_t r = base + i * kContribThreads;
       const int64_t rc = r < n_rows ? r : n_rows - 1;
 #pragma unroll
       for (int j = 0; j < NMAX; ++j) {
@@ -144,9 +148,12 @@ __device__ void weights_block(const MergeArgs& a) {
         if (j < n) lv[i][j] = a.lse[(int64_t)a.slots[j] * n_rows + rc];
       }
     }
+    float acc[NMAX];
+#pragma unroll
+    for (int j = 0; j < NMAX; ++j) acc[j] = 0.f;
 #pragma unroll
     for (int i = 0; i < R; ++i) {
-      const bool ok = base + i * kMergeThreads < n_rows;
+      const bool ok = base + i * kContribThreads < n_rows;
       float e[NMAX], tot;
 #pragma unroll
       for (int j = 0; j < NMAX; ++j) e[j] = lv[i][j];
@@ -155,23 +162,56 @@ __device__ void weights_block(const MergeArgs& a) {
       for (int j = 0; j < NMAX; ++j)
         if (j < n) acc[j] += ok ? weight_of(lv[i][j], lo) : 0.f;
     }
-  }
-  float mine = 0.f;                      // lane j: the sum of slot j
+    float mine = 0.f;                    // lane j: the sum of slot j
 #pragma unroll
-  for (int j = 0; j < NMAX; ++j)
-    if (j < n) {
-      const float t = wave_sum(acc[j]);
-      mine = lane == j ? t : mine;
-    }
-  if (lane < n)
-    __hip_atomic_fetch_add(a.w_sum + lane, (uint64_t)(mine * 4294967296.f), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int j = 0; j < NMAX; ++j)
+      if (j < n) {
+        const float t = wave_sum(acc[j]);
+        mine = lane == j ? t : mine;
+      }
+    if (lane < n)
+      __hip_atomic_store(a.w_partial + (int64_t)u * n + lane, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   int done = 0;
   if (lane == 0) done = __hip_atomic_fetch_add(a.w_count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (__builtin_amdgcn_readfirstlane(done) != a.n_wblocks - 1) return;
-  if (lane < n) {
-    const uint64_t sum = __hip_atomic_exchange(a.w_sum + lane, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    a.w_part[lane] = (float)((double)sum * (1.0 / 4294967296.0) / (double)n_rows);
+  constexpr int G = NMAX < 8 ? NMAX : 8;               // slots whose loads are in flight together
+#pragma unroll 1
+  for (int j0 = 0; j0 < n; j0 += G) {
+    float sum[G];
+#pragma unroll
+    for (int j = 0; j < G; ++j) sum[j] = 0.f;
+    // thread w * 64 + lane of contrib_final_kernel takes the blocks at that
+    // distance; waves without a block add nothing
+#pragma unroll 1
+    for (int w = 0; w < kContribWaves && w * 64 < a.w_blocks; ++w) {
+      float acc[G];
+#pragma unroll
+      for (int j = 0; j < G; ++j) acc[j] = 0.f;
+#pragma unroll 1
+      for (int b0 = w * 64; b0 < a.w_blocks; b0 += kContribThreads) {
+        const float* p = a.w_partial + (int64_t)min(b0 + lane, a.w_blocks - 1) * kContribWaves * n;
+        float x[kContribWaves][G];
+#pragma unroll
+        for (int v = 0; v < kContribWaves; ++v)
+#pragma unroll
+          for (int j = 0; j < G; ++j)
+            x[v][j] = __hip_atomic_load(p + v * n + min(j0 + j, n - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+          float block = 0.f;
+#pragma unroll
+          for (int v = 0; v < kContribWaves; ++v) block += x[v][j];
+          acc[j] += b0 + lane < a.w_blocks ? block : 0.f;
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < G; ++j) sum[j] += wave_sum(acc[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < G; ++j)
+      if (lane == 0 && j0 + j < n) a.w_part[j0 + j] = sum[j] / (float)n_rows;
   }
   if (lane == 0) __hip_atomic_store(a.w_count, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -313,10 +353,6 @@ hipError_t launch_merge_d(const MergeArgs& a, int D, hipStream_t s) {
 // with a butterfly over the wave (lane l adds lane l^k's value, so every lane
 // holds the same bits) and the waves' sums are added in wave order: one
 // barrier for all partitions, and bitwise the same result on every run.
-constexpr int kContribThreads = 256;
-constexpr int kContribRowsPerThread = 2;
-constexpr int kContribRowsPerBlock = kContribThreads * kContribRowsPerThread;
-constexpr int kContribWaves = kContribThreads / 64;
 
 // Per-row weights are written through LDS, 16 partitions at a time: a wave's
 // 64 rows x P floats are consecutive in memory, and its lanes write them in
@@ -458,20 +494,23 @@ hipError_t launch_merge(const MergeArgs& a, ditango_dtype sdt, ditango_dtype odt
   return hipErrorInvalidValue;
 }
 
-// Up to 128 weight workgroups, each taking as many rounds of rows as that
-// needs.  They come first in the grid and run beside the composition; what
-// limits their number is the additions to one line of memory from all XCDs:
-// 9,450 rows x 40 heads x 8 slots, composition alone 140 us, with weights
-// 141 / 143 / 148 / 160 us with up to 128 / 256 / 512 / 1,024 of them (149
-// with the two weight kernels after it); 8,192 x 24 x 16: 146 alone, 148 /
-// 148 / 151 / 165 (157); 2,048 x 12 x 8 at D=64: 5.9 alone, 9.6 (13.0).
-constexpr int kComposeBlocks = 128;
-int compose_wblocks(int64_t n_rows, int n, int* iters) {
-  const int64_t per = kMergeThreads * weight_rows(n);
-  const int64_t rounds = (n_rows + per - 1) / per;
-  const int64_t it = (rounds + kComposeBlocks - 1) / kComposeBlocks;
+// Up to 256 weight workgroups, each taking as many units as that needs.  They
+// come first in the grid and run beside the composition; more of them contend
+// for the counter's line, fewer take longer than the composition (9,450 rows x
+// 40 heads x 8 slots, composition alone 138 us, with weights 140 / 143 / 207 us
+// with up to 256 / 128 / 64 of them, 145 with the two weight kernels after it;
+// 8,192 x 24 x 16: 145 alone, 147 / 154 / 216, 156; 2,048 x 12 x 8 at D=64:
+// 6.0 alone, 11.0 / 12.6 / 15.2, 13.1).
+constexpr int kComposeBlocks = 256;
+int compose_wblocks(int64_t n_rows, int* iters) {
+  const int64_t units = contrib_blocks(n_rows) * kContribWaves;
+  const int64_t it = (units + kComposeBlocks - 1) / kComposeBlocks;
   *iters = (int)it;
-  return (int)((rounds + it - 1) / it);
+  return (int)((units + it - 1) / it);
+}
+
+size_t compose_ws_bytes(int64_t n_rows, int n) {
+  return kComposeCountBytes + (size_t)contrib_blocks(n_rows) * kContribWaves * n * sizeof(float);
 }
 
 int64_t contrib_blocks(int64_t n_rows) { return (n_rows + kContribRowsPerBlock - 1) / kContribRowsPerBlock; }

@@ -149,6 +149,6 @@ class GroupedSelectiveAttention:
         # composition and the weights of the live groups
         w = torch.empty(len(slots), dtype=torch.float32, device=self.device)
         if self._ws is None:
-            self._ws = api.compose_workspace(self.device)
+            self._ws = api.compose_workspace(self.B, self.H, self.L, self.P, self.device)
         api.compose(self.out, self.lse, out, lse, w, self._ws, slots=slots)
         return out, lse, w

@@ -85,9 +85,11 @@ def test_norms_of_slots_sharing_a_reference(dtype, n):
 
 @pytest.mark.parametrize("dtype,D,B,L,H,P,slots", [
     ("bf16", 128, 1, 1, 1, 1, None),                      # one row, one weight workgroup
-    ("bf16", 64, 2, 43, 3, 8, [6, 1, 3]),                 # 258 rows: a partial third workgroup of 128
-    ("f32", 64, 1, 1025, 16, 4, None),                    # 16,400 rows: 129 rounds, two per workgroup
-    ("bf16", 128, 2, 900, 10, 9, [8, 0, 2, 4, 1, 7, 3, 5, 6]),   # 64 rows per round beyond 8 slots
+    ("bf16", 64, 2, 43, 3, 8, [6, 1, 3]),                 # 258 rows: part of a row block of 512
+    ("f32", 64, 1, 1025, 16, 4, None),                    # 16,400 rows: 33 row blocks
+    ("bf16", 64, 1, 4150, 16, 2, None),                   # 66,400 rows: 130 blocks, two per workgroup
+    ("bf16", 64, 1, 9000, 16, 9, None),                   # 282 blocks: more than one round of final sums
+    ("bf16", 128, 2, 900, 10, 9, [8, 0, 2, 4, 1, 7, 3, 5, 6]),
     ("f32", 128, 1, 130, 2, 20, None),
     ("bf16", 64, 1, 70, 2, 64, None),
 ])
@@ -106,8 +108,11 @@ def test_compose_is_merge_and_weights(dtype, D, B, L, H, P, slots):
     api.merge_states(st, lse, ref, lref, slots=slots)
     ll = lse[listed].double()
     w64 = torch.exp(ll - torch.logsumexp(ll, 0)).nan_to_num(0.0).mean((1, 2, 3))
-    ws = api.compose_workspace()
-    first = None
+    ws = api.compose_workspace(B, H, L, len(listed))
+    # the weights kernels on the listed log-sum-exps, bit for bit
+    cw = torch.empty(api.contrib_workspace_bytes(B, H, L, len(listed)), dtype=torch.uint8, device="cuda")
+    first = torch.empty(len(listed), device="cuda")
+    api.contrib(lse[listed].contiguous(), lref, first, cw)
     for _ in range(3):                                    # one workspace, left as it was found
         w = torch.full((len(listed),), 7.0, device="cuda")
         out.fill_(3.0)
@@ -115,8 +120,7 @@ def test_compose_is_merge_and_weights(dtype, D, B, L, H, P, slots):
         api.compose(st, lse, out, lo, w, ws, slots=slots)
         assert torch.equal(out, ref) and torch.equal(lo.view(torch.int32), lref.view(torch.int32))
         assert float((w.double() - w64).abs().max()) <= 1e-6
-        assert int(ws.to(torch.int32).sum()) == 0
-        first = w.clone() if first is None else first
+        assert int(ws[:256].to(torch.int32).sum()) == 0
         assert torch.equal(w, first)
     api.compose(st, lse, out, None, w, ws, slots=slots)   # without the composed log-sum-exps
     assert torch.equal(w, first) and torch.equal(out, ref)
@@ -130,7 +134,7 @@ def test_compose_captured_in_a_graph():
     st = torch.randn((P, B, L, H, D), generator=g, device="cuda").to(torch.bfloat16)
     lse = torch.randn((P, B, H, L), generator=g, device="cuda")
     out = torch.empty((B, L, H, D), dtype=torch.bfloat16, device="cuda")
-    lo, w, ws = torch.empty((B, H, L), device="cuda"), torch.empty(P, device="cuda"), api.compose_workspace()
+    lo, w, ws = torch.empty((B, H, L), device="cuda"), torch.empty(P, device="cuda"), api.compose_workspace(B, H, L, P)
     api.compose(st, lse, out, lo, w, ws)
     torch.cuda.synchronize()
     graph = torch.cuda.CUDAGraph()
