@@ -205,17 +205,16 @@ size_t ditango_compose_workspace_bytes(int B, int H, int64_t q_len, int n_slots)
 
 /*
  * ditango_merge_states and the listed slots' mean contribution weights
- * (Sec. 4.1.2, Eq. lse_weight) in one launch:
+ * (Sec. 4.1.2, Eq. lse_weight) in one call:
  *     w_part[i] = mean over all B*H*q_len rows of exp(LSE_slots[i] - LSE).
  * Reduced in the order of ditango_contrib: the same bits as ditango_contrib
  * over those slots' LSEs, on every run.
  *
  *   w_part     device, [n_slots] float32 (n_slots = P when slots is NULL).
  *   workspace  device, ditango_compose_workspace_bytes(...) bytes, 256-byte
- *              aligned.  Its first 256 bytes hold a counter, which the caller
- *              zeroes once, after allocating it; every call leaves it zero for
- *              the next, of any size the workspace holds.  Calls that overlap
- *              on one workspace race.
+ *              aligned; its contents do not matter.  Calls that overlap on
+ *              one workspace race for their own weights, and no later call
+ *              is touched by that.
  * The other arguments are those of ditango_merge_states, except that `out` /
  * `lse_out` may not be a listed slot (DITANGO_ERR_INVALID).
  */

@@ -167,8 +167,8 @@ def merge_states(out_states: torch.Tensor, lse_states: torch.Tensor, out: torch.
 
 
 def compose_workspace(B: int, H: int, q_len: int, n_slots: int, device="cuda") -> torch.Tensor:
-    """A workspace for ``compose`` of these sizes, its counter zeroed; it
-    serves any number of calls that do not overlap."""
+    """A workspace for ``compose`` of these sizes; it serves any number of
+    calls that do not overlap, and its contents do not matter."""
     return torch.zeros(int(_lib.lib().ditango_compose_workspace_bytes(B, H, q_len, n_slots)), dtype=torch.uint8,
                        device=device)
 
@@ -177,7 +177,7 @@ def compose(out_states: torch.Tensor, lse_states: torch.Tensor, out: torch.Tenso
             w_part: torch.Tensor, workspace: torch.Tensor, slots: Optional[Sequence[int]] = None) -> None:
     """Composition of the listed slots (default: all) into ``out``/``lse_out``
     and the listed slots' mean contribution weights into ``w_part``, in one
-    launch (ditango_compose).  ``workspace`` comes from compose_workspace."""
+    call (ditango_compose).  ``workspace`` comes from compose_workspace."""
     _dev(out_states, lse_states, out, lse_out, w_part, workspace)
     P, B, q_len, H, D = out_states.shape
     if tuple(lse_states.shape) != (P, B, H, q_len) or lse_states.dtype != torch.float32:

@@ -234,9 +234,8 @@ ditango_status ditango_compose(
   a.w_blocks = (int)nb;
   a.n_wblocks = compose_wblocks(a.rows, &a.w_iters);
   a.w_part = w_part;
-  a.w_count = (int*)workspace;
-  a.w_partial = (float*)((char*)workspace + kComposeCountBytes);
-  return from_hip(launch_merge(a, state_dt, out_dt, D, (hipStream_t)stream));
+  a.w_partial = (float*)((char*)workspace + kComposeHeadBytes);
+  return from_hip(launch_compose(a, state_dt, out_dt, D, (hipStream_t)stream));
 }
 
 size_t ditango_contrib_workspace_bytes(int B, int H, int64_t q_len, int P) {

@@ -124,7 +124,6 @@ struct MergeArgs {
   int w_blocks;
   float* w_part;            // [n]
   float* w_partial;         // workspace [units][n]
-  int* w_count;             // finished weight workgroups; 0 before and after the launch
 };
 
 struct ContribArgs {
@@ -160,7 +159,7 @@ int64_t contrib_blocks(int64_t n_rows);
 // each takes, and the workspace's bytes for n slots.
 int compose_wblocks(int64_t n_rows, int* iters);
 size_t compose_ws_bytes(int64_t n_rows, int n);
-constexpr size_t kComposeCountBytes = 256;   // the counter, at the start of the workspace
+constexpr size_t kComposeHeadBytes = 256;   // left alone, at the start of the workspace
 
 // bf16 inputs; states in bf16, or in float32 when state_f32
 hipError_t launch_attn_bf16(const AttnArgs& a, int D, bool state_f32, hipStream_t s);
@@ -176,6 +175,8 @@ hipError_t launch_attn_bf16_ws(const AttnArgs& a, int D, bool state_f32, void* w
 hipError_t launch_attn_f32(const AttnArgs& a, int D, hipStream_t s);
 hipError_t launch_merge(const MergeArgs& a, ditango_dtype sdt, ditango_dtype odt, int D,
                         hipStream_t s);
+// launch_merge with weight workgroups, then the weights' final sums.
+hipError_t launch_compose(const MergeArgs& a, ditango_dtype sdt, ditango_dtype odt, int D, hipStream_t s);
 hipError_t launch_contrib(const ContribArgs& a, hipStream_t s);
 // Device address, on the current device, of the fixed scratch array of the
 // allocation-free contrib entry point (kContribScratchBytes); looked up once

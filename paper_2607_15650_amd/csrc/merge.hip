@@ -11,6 +11,8 @@
 // anchor weights of Eq. lse_weight) and their mean over all rows per
 // partition, reduced in a fixed order (per workgroup, then one workgroup per
 // partition over the partial sums) so results are bitwise reproducible.
+#include <string.h>
+
 #include <mutex>
 
 #include "internal.h"
@@ -114,19 +116,15 @@ constexpr int kContribRowsPerThread = 2;
 constexpr int kContribRowsPerBlock = kContribThreads * kContribRowsPerThread;
 constexpr int kContribWaves = kContribThreads / 64;
 
-// One weight workgroup (one wave) of a composition with weights: mean weights
-// of the listed slots over all rows, in one launch with the composition.  The
-// wave composes its rows' log-sum-exps itself (the composed ones are being
-// written by other workgroups), forms the sums of w_iters units - a unit is
-// what one of the kContribWaves waves of a contrib_partial_kernel workgroup
-// takes - and publishes them; the wave that finds all others finished adds
-// them up as those workgroups and contrib_final_kernel do, and leaves the
-// counter at zero for the next launch.
-//
-// The sums and the counter are read and written with device-scope atomics
-// only: the XCDs' L2 caches are not coherent with each other, and an atomic's
-// result is in none of them.  A wave's sums are complete (vmcnt) before it
-// counts itself finished.
+// One weight workgroup (one wave) of a composition with weights.  The wave
+// composes its rows' log-sum-exps itself (the composed ones are being written
+// by other workgroups) and forms the sums of w_iters units - a unit is what
+// one of the kContribWaves waves of a contrib_partial_kernel workgroup takes.
+// contrib_final_kernel, launched after the composition, adds them up.  (The
+// last of these waves to finish could do that itself and spare the launch,
+// but only by a counter that has to be zero when the call begins: memory that
+// was never written, a call that was interrupted, or two calls that overlap on
+// a workspace then leave every later call without weights.)
 template <int NMAX>
 __device__ void weights_block(const MergeArgs& a) {
   constexpr int R = kContribRowsPerThread;
@@ -169,51 +167,8 @@ __device__ void weights_block(const MergeArgs& a) {
         const float t = wave_sum(acc[j]);
         mine = lane == j ? t : mine;
       }
-    if (lane < n)
-      __hip_atomic_store(a.w_partial + (int64_t)u * n + lane, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (lane < n) a.w_partial[(int64_t)u * n + lane] = mine;
   }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  int done = 0;
-  if (lane == 0) done = __hip_atomic_fetch_add(a.w_count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (__builtin_amdgcn_readfirstlane(done) != a.n_wblocks - 1) return;
-  constexpr int G = NMAX < 8 ? NMAX : 8;               // slots whose loads are in flight together
-#pragma unroll 1
-  for (int j0 = 0; j0 < n; j0 += G) {
-    float sum[G];
-#pragma unroll
-    for (int j = 0; j < G; ++j) sum[j] = 0.f;
-    // thread w * 64 + lane of contrib_final_kernel takes the blocks at that
-    // distance; waves without a block add nothing
-#pragma unroll 1
-    for (int w = 0; w < kContribWaves && w * 64 < a.w_blocks; ++w) {
-      float acc[G];
-#pragma unroll
-      for (int j = 0; j < G; ++j) acc[j] = 0.f;
-#pragma unroll 1
-      for (int b0 = w * 64; b0 < a.w_blocks; b0 += kContribThreads) {
-        const float* p = a.w_partial + (int64_t)min(b0 + lane, a.w_blocks - 1) * kContribWaves * n;
-        float x[kContribWaves][G];
-#pragma unroll
-        for (int v = 0; v < kContribWaves; ++v)
-#pragma unroll
-          for (int j = 0; j < G; ++j)
-            x[v][j] = __hip_atomic_load(p + v * n + min(j0 + j, n - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-        for (int j = 0; j < G; ++j) {
-          float block = 0.f;
-#pragma unroll
-          for (int v = 0; v < kContribWaves; ++v) block += x[v][j];
-          acc[j] += b0 + lane < a.w_blocks ? block : 0.f;
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < G; ++j) sum[j] += wave_sum(acc[j]);
-    }
-#pragma unroll
-    for (int j = 0; j < G; ++j)
-      if (lane == 0 && j0 + j < n) a.w_part[j0 + j] = sum[j] / (float)n_rows;
-  }
-  if (lane == 0) __hip_atomic_store(a.w_count, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Each thread owns 8 elements of one row (row = (b*q_len + r)*H + h,
@@ -454,14 +409,24 @@ __global__ __launch_bounds__(kContribThreads) void contrib_partial_kernel(const 
   }
 }
 
-// The workgroups' partial sums added in a fixed order, one workgroup per
-// partition (thread t takes partials t, t + kContribThreads, ...).
+// The row blocks' sums added in a fixed order, one workgroup per partition
+// (thread t takes blocks t, t + kContribThreads, ...).  A block's sum is one
+// partial, or (UNITS > 1) that many, added in order.
+template <int UNITS>
 __global__ __launch_bounds__(kContribThreads) void contrib_final_kernel(const ContribArgs a) {
   __shared__ float red[kContribWaves];
   const int tid = threadIdx.x;
   const int P = a.P, j = blockIdx.x;
   float acc = 0.f;
-  for (int blk = tid; blk < a.n_blocks; blk += kContribThreads) acc += a.partial[(int64_t)blk * P + j];
+  for (int blk = tid; blk < a.n_blocks; blk += kContribThreads) {
+    const float* p = a.partial + (int64_t)blk * UNITS * P + j;
+    float x[UNITS], block = 0.f;
+#pragma unroll
+    for (int v = 0; v < UNITS; ++v) x[v] = p[v * P];
+#pragma unroll
+    for (int v = 0; v < UNITS; ++v) block += x[v];
+    acc += block;
+  }
   acc = wave_sum(acc);
   if ((tid & 63) == 0) red[tid >> 6] = acc;
   __syncthreads();
@@ -480,7 +445,7 @@ hipError_t launch_contrib_t(const ContribArgs& a, hipStream_t s) {
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(contrib_final_kernel, dim3(a.P), dim3(kContribThreads), 0, s, a);
+  hipLaunchKernelGGL(contrib_final_kernel<1>, dim3(a.P), dim3(kContribThreads), 0, s, a);
   return hipGetLastError();
 }
 
@@ -494,13 +459,28 @@ hipError_t launch_merge(const MergeArgs& a, ditango_dtype sdt, ditango_dtype odt
   return hipErrorInvalidValue;
 }
 
+hipError_t launch_compose(const MergeArgs& a, ditango_dtype sdt, ditango_dtype odt, int D, hipStream_t s) {
+  const hipError_t e = launch_merge(a, sdt, odt, D, s);
+  if (e != hipSuccess) return e;
+  ContribArgs c;
+  memset(&c, 0, sizeof(c));
+  c.w_part = a.w_part;
+  c.partial = a.w_partial;
+  c.n_rows = a.rows;
+  c.P = a.n;
+  c.n_blocks = a.w_blocks;
+  hipLaunchKernelGGL(contrib_final_kernel<kContribWaves>, dim3(c.P), dim3(kContribThreads), 0, s, c);
+  return hipGetLastError();
+}
+
 // Up to 256 weight workgroups, each taking as many units as that needs.  They
-// come first in the grid and run beside the composition; more of them contend
-// for the counter's line, fewer take longer than the composition (9,450 rows x
-// 40 heads x 8 slots, composition alone 138 us, with weights 140 / 143 / 207 us
-// with up to 256 / 128 / 64 of them, 145 with the two weight kernels after it;
-// 8,192 x 24 x 16: 145 alone, 147 / 154 / 216, 156; 2,048 x 12 x 8 at D=64:
-// 6.0 alone, 11.0 / 12.6 / 15.2, 13.1).
+// come first in the grid and run beside the composition; fewer take longer
+// than the composition, more hold up its first workgroups (9,450 rows x 40
+// heads x 8 slots at D=128: composition alone 140 us, with weights 145 / 142 /
+// 143 / 145 us with up to 128 / 256 / 512 / 1,024 of them, 150 with the two
+// weight kernels after it; 14,850 x 48 x 8 at D=64: 148 alone, 205 / 156 / 153
+// / 154, 161; 2,048 x 12 x 8 at D=64: 6.0 alone, 11.2 / 8.4 / 8.4 / 8.4, 12.8;
+// 3,000 x 12 x 20 at D=128: 43.3 alone, 49.5 / 45.7 / 45.9 / 45.8, 59.1).
 constexpr int kComposeBlocks = 256;
 int compose_wblocks(int64_t n_rows, int* iters) {
   const int64_t units = contrib_blocks(n_rows) * kContribWaves;
@@ -510,7 +490,7 @@ int compose_wblocks(int64_t n_rows, int* iters) {
 }
 
 size_t compose_ws_bytes(int64_t n_rows, int n) {
-  return kComposeCountBytes + (size_t)contrib_blocks(n_rows) * kContribWaves * n * sizeof(float);
+  return kComposeHeadBytes + (size_t)contrib_blocks(n_rows) * kContribWaves * n * sizeof(float);
 }
 
 int64_t contrib_blocks(int64_t n_rows) { return (n_rows + kContribRowsPerBlock - 1) / kContribRowsPerBlock; }

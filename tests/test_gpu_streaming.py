@@ -148,3 +148,64 @@ def test_compose_captured_in_a_graph():
         replayed = (out.clone(), lo.clone(), w.clone())
         api.compose(st, lse, out, lo, w, ws)              # eager work on the same workspace between
         assert all(torch.equal(a, b) for a, b in zip(replayed, (out, lo, w))), i
+
+
+@pytest.mark.parametrize("n", [1, 8, 16, 20, 40])
+def test_compose_needs_nothing_of_its_workspace(n):
+    """Whatever the workspace holds (memory that was never written, what an
+    interrupted or overlapping call left), the weights are those of the weight
+    kernels."""
+    import torch
+    from paper_2607_15650_amd import api
+    B, L, H, D = 1, 700, 5, 64
+    g = torch.Generator(device="cuda").manual_seed(n)
+    st = torch.randn((n, B, L, H, D), generator=g, device="cuda").to(torch.bfloat16)
+    lse = torch.randn((n, B, H, L), generator=g, device="cuda")
+    out = torch.empty((B, L, H, D), dtype=torch.bfloat16, device="cuda")
+    lo, first = torch.empty((B, H, L), device="cuda"), torch.empty(n, device="cuda")
+    api.merge_states(st, lse, out, lo)
+    cw = torch.empty(api.contrib_workspace_bytes(B, H, L, n), dtype=torch.uint8, device="cuda")
+    api.contrib(lse, lo, first, cw)
+    ws = api.compose_workspace(B, H, L, n)
+    for fill in (0xFF, 0x01, 0x7F, 0x00):
+        ws.fill_(fill)
+        w = torch.full((n,), 7.0, device="cuda")
+        api.compose(st, lse, out, lo, w, ws)
+        assert torch.equal(w, first), fill
+
+
+@pytest.mark.parametrize("grouped", [False, True])
+def test_first_composition_inside_a_capture(grouped):
+    """An engine whose first step is captured: an eager step before any replay,
+    and every replay, give the weights of an engine that never captured."""
+    import torch
+    from paper_2607_15650_amd.groups import GroupedSelectiveAttention
+    from paper_2607_15650_amd.step import SelectiveAttention
+    H, D, offs = 3, 64, [0, 130, 260, 390, 520]
+    g = torch.Generator(device="cuda").manual_seed(3)
+    q, k, v = (torch.randn((1, 520, H, D), generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+
+    def engine():
+        if grouped:
+            e = GroupedSelectiveAttention(1, H, D, offs, 1, 1, D ** -0.5)
+            return lambda t: e.step(t, q, k, v, e.groups)[2]
+        e = SelectiveAttention(1, H, D, offs, D ** -0.5)
+        e.cache(1)
+        return lambda t: e.step(t, 1, q, k, v, [1, 1, 1, 1])[2]
+
+    ref = engine()(0).clone()
+    step = engine()
+    torch.cuda.synchronize()
+    # memory the captured step may be given holds anything
+    junk = torch.full((1 << 22,), 0x5A, dtype=torch.uint8, device="cuda")
+    del junk
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        w = step(0)
+    assert torch.equal(step(1), ref)
+    for i in range(3):
+        w.fill_(9.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(w, ref), i
+        assert torch.equal(step(2 + i), ref), i
