@@ -189,16 +189,26 @@ __device__ void weights_block(const MergeArgs& a) {
 // a handful) use a small, high-occupancy instantiation.  IDX32: row and LSE
 // indices in 32-bit arithmetic (a 64-bit division by a run-time value is a
 // long instruction sequence in front of the LSE loads).
-template <typename TS, typename TO, int D, int NMAX, bool IDX32>
+// W: with weight workgroups, in instances of their own: a composition without
+// weights keeps its registers and waves (bf16 states, 4 / 8 / 16 / 64 slots:
+// 35 / 55 / 65 / 142 registers; 60 / 100 / 101 / 196 while it carried the
+// weights' code.  3,000 rows x 12 heads x 20 slots at D=128 43.4 -> 36.9 us,
+// 4,095 x 12 x 5 14.9 -> 13.4; 9,450 x 40 x 8 138.0 -> 139.0: a launch that
+// HBM bounds alone gains nothing from more waves).
+template <typename TS, typename TO, int D, int NMAX, bool IDX32, bool W>
 __global__ __launch_bounds__(kMergeThreads) void merge_kernel(const MergeArgs a) {
   constexpr int CPR = D / 8;                      // chunks (lanes) per row
   using CK = Chunk8<TS, D>;
-  if ((int)blockIdx.x < a.n_wblocks) {
-    weights_block<NMAX>(a);
-    return;
+  int block = (int)blockIdx.x;
+  if constexpr (W) {
+    block -= a.n_wblocks;
+    if (block < 0) {
+      weights_block<NMAX>(a);
+      return;
+    }
   }
   const int n = a.n;
-  const int64_t c = (int64_t)(blockIdx.x - a.n_wblocks) * kMergeThreads + threadIdx.x;
+  const int64_t c = (int64_t)block * kMergeThreads + threadIdx.x;
   const bool live = c < a.rows * CPR;
   const int64_t row = live ? c / CPR : 0;
   const int ch = (int)(c % CPR);
@@ -269,16 +279,16 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(const MergeArgs a)
   }
 }
 
-template <typename TS, typename TO, int D, bool IDX32>
+template <typename TS, typename TO, int D, bool IDX32, bool W>
 void launch_merge_n(const MergeArgs& a, dim3 g, dim3 t, hipStream_t s) {
   if (a.n <= 4)
-    hipLaunchKernelGGL((merge_kernel<TS, TO, D, 4, IDX32>), g, t, 0, s, a);
+    hipLaunchKernelGGL((merge_kernel<TS, TO, D, 4, IDX32, W>), g, t, 0, s, a);
   else if (a.n <= 8)
-    hipLaunchKernelGGL((merge_kernel<TS, TO, D, 8, IDX32>), g, t, 0, s, a);
+    hipLaunchKernelGGL((merge_kernel<TS, TO, D, 8, IDX32, W>), g, t, 0, s, a);
   else if (a.n <= 16)
-    hipLaunchKernelGGL((merge_kernel<TS, TO, D, 16, IDX32>), g, t, 0, s, a);
+    hipLaunchKernelGGL((merge_kernel<TS, TO, D, 16, IDX32, W>), g, t, 0, s, a);
   else
-    hipLaunchKernelGGL((merge_kernel<TS, TO, D, kMaxParts, IDX32>), g, t, 0, s, a);
+    hipLaunchKernelGGL((merge_kernel<TS, TO, D, kMaxParts, IDX32, W>), g, t, 0, s, a);
 }
 
 template <typename TS, typename TO, int D>
@@ -287,10 +297,18 @@ hipError_t launch_merge_t(const MergeArgs& a, hipStream_t s) {
   if (blocks == 0) return hipSuccess;
   if (blocks + a.n_wblocks > 0x7fffffff) return hipErrorInvalidConfiguration;
   const dim3 g((unsigned)(blocks + a.n_wblocks)), t(kMergeThreads);
-  if (a.rows < 0x7fffffffLL && (int64_t)a.B * a.H * a.q_len < 0x7fffffffLL)
-    launch_merge_n<TS, TO, D, true>(a, g, t, s);
-  else
-    launch_merge_n<TS, TO, D, false>(a, g, t, s);
+  const bool idx32 = a.rows < 0x7fffffffLL;
+  if (a.n_wblocks > 0) {
+    if (idx32)
+      launch_merge_n<TS, TO, D, true, true>(a, g, t, s);
+    else
+      launch_merge_n<TS, TO, D, false, true>(a, g, t, s);
+  } else {
+    if (idx32)
+      launch_merge_n<TS, TO, D, true, false>(a, g, t, s);
+    else
+      launch_merge_n<TS, TO, D, false, false>(a, g, t, s);
+  }
   return hipGetLastError();
 }
 
