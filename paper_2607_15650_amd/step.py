@@ -78,17 +78,7 @@ class SelectiveAttention:
         out = torch.empty((self.B, L, self.H, self.D), dtype=self.dtype, device=self.device)
         lse = torch.empty((self.B, self.H, L), dtype=torch.float32, device=self.device)
         w_part = torch.empty(self.P, dtype=torch.float32, device=self.device)
-        if self.P <= 16:
-            if L not in self._ws:
-                self._ws[L] = api.compose_workspace(self.B, self.H, L, self.P, self.device)
-            api.compose(c.out, c.lse, out, lse, w_part, self._ws[L])
-        else:
-            # beyond 16 slots the weights of the one-launch form take longer
-            # than the kernels of their own (20 slots, 300 rows x 2 heads:
-            # 26.2 us against 23.2 for both)
-            api.merge_states(c.out, c.lse, out, lse)
-            if L not in self._ws:
-                n = api.contrib_workspace_bytes(self.B, self.H, L, self.P)
-                self._ws[L] = torch.empty(max(16, n), dtype=torch.uint8, device=self.device)
-            api.contrib(c.lse, lse, w_part, self._ws[L])
+        if L not in self._ws:
+            self._ws[L] = api.compose_workspace(self.B, self.H, L, self.P, self.device)
+        api.compose(c.out, c.lse, out, lse, w_part, self._ws[L])
         return out, lse, w_part
