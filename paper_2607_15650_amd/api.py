@@ -13,7 +13,7 @@ Layouts (all tensors contiguous, on the same GPU):
 from __future__ import annotations
 
 import ctypes
-from typing import Optional, Sequence
+from typing import Optional, Sequence, Tuple
 
 import torch
 
@@ -119,6 +119,16 @@ def attn_partition_states(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor,
             offs, P, sel, float(scale), out_states.data_ptr(), _dtype(out_states), lse_states.data_ptr(),
             _stream())
         _lib.check("ditango_attn_partition_states_ex", st)
+
+
+def query_block(q_all: torch.Tensor, begin: int, length: int) -> Tuple[torch.Tensor, int]:
+    """Rows [begin, begin + length) of every batch as (query tensor, first row)
+    for attn_block_states: ``q_all`` itself, read in place, or a copy of the
+    rows where it is not contiguous or not 16-byte aligned (the kernels load
+    16 bytes at a time)."""
+    if q_all.is_contiguous() and q_all.data_ptr() % 16 == 0:
+        return q_all, begin
+    return q_all[:, begin:begin + length].clone(memory_format=torch.contiguous_format), 0
 
 
 def attn_block_states(q_all: torch.Tensor, q_begin: int, q_len: int, k: torch.Tensor, v: torch.Tensor,

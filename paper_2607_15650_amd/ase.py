@@ -126,8 +126,7 @@ class ErrorModelSelectiveAttention:
         """Returns (OUT, LSE, info) with info = dict(anchor, compute, ase, eps, drift), and,
         when the model is evaluated, ``measured`` (group -> the error its cached
         state actually carries) at every step after the first."""
-        a, e = self.offsets[self.q], self.offsets[self.q + 1]
-        qb = (q_all, a) if q_all.is_contiguous() else (q_all[:, a:e].contiguous(), 0)
+        qb = api.query_block(q_all, self.offsets[self.q], self.L)
         loc = [0] * self.P
         loc[self.q] = 1
         self._attn(qb, k, v, loc, self.cache, self.cache_lse)          # local partition first

@@ -131,13 +131,10 @@ class GroupedSelectiveAttention:
             if grp in compute:
                 for j in range(*grp):
                     sel[j] = 1
-        a, e = self.offsets[self.q], self.offsets[self.q + 1]
+        a = self.offsets[self.q]
         ws = self._attn_ws.get(q_all.dtype, self.B, self.H, self.D, self.L, self.offsets, sel)
-        if q_all.is_contiguous():
-            api.attn_block_states(q_all, a, self.L, k, v, self.offsets, sel, self.scale, self.out, self.lse, ws)
-        else:
-            qb = q_all[:, a:e].contiguous()
-            api.attn_partition_states(qb, k, v, self.offsets, sel, self.scale, self.out, self.lse, ws)
+        q, q0 = api.query_block(q_all, a, self.L)
+        api.attn_block_states(q, q0, self.L, k, v, self.offsets, sel, self.scale, self.out, self.lse, ws)
         for grp in self.groups:
             if grp in compute:
                 if grp[1] - grp[0] > 1:

@@ -66,11 +66,8 @@ class SelectiveAttention:
         c = self.cache(qb)
         a, e = self.offsets[qb], self.offsets[qb + 1]
         ws = self._attn_ws.get(q_all.dtype, self.B, self.H, self.D, e - a, self.offsets, select)
-        if q_all.is_contiguous():
-            api.attn_block_states(q_all, a, e - a, k, v, self.offsets, select, self.scale, c.out, c.lse, ws)
-        else:
-            q = q_all[:, a:e].contiguous()
-            api.attn_partition_states(q, k, v, self.offsets, select, self.scale, c.out, c.lse, ws)
+        q, q0 = api.query_block(q_all, a, e - a)
+        api.attn_block_states(q, q0, e - a, k, v, self.offsets, select, self.scale, c.out, c.lse, ws)
         for j, s in enumerate(select):
             if s:
                 c.computed_at[j] = step

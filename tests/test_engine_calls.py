@@ -38,3 +38,21 @@ def test_composition_and_weights_are_one_call(calls, kind, P):
     q = torch.zeros((1, 4 * P, 1, 64), dtype=torch.bfloat16)
     run(kind, P, q)
     assert [n for n, _ in calls] == ["attn_block_states", "compose"]
+
+
+@pytest.mark.parametrize("kind", ["step", "group"])
+@pytest.mark.parametrize("B", [1, 2])
+@pytest.mark.parametrize("shift,strided", [(0, False), (1, False), (4, False), (8, False), (0, True)])
+def test_query_block_is_in_place_or_an_aligned_copy(calls, kind, B, shift, strided):
+    """Read in place where the kernels' 16-byte loads can read it, otherwise a
+    copy of the block's rows; the rows handed over are the block's either way."""
+    P, n = 3, B * 12 * 64
+    flat = torch.arange(2 * n + 8, dtype=torch.float32).to(torch.bfloat16)
+    q = flat[shift:shift + 2 * n:2].view(B, 12, 1, 64) if strided else flat[shift:shift + n].view(B, 12, 1, 64)
+    run(kind, P, q, B)
+    name, args = calls[0]
+    assert name == "attn_block_states"
+    got, begin, length = args[:3]
+    assert got.is_contiguous() and got.data_ptr() % 16 == 0 and length == 4
+    assert torch.equal(got[:, begin:begin + length], q[:, 4:8])
+    assert (got.data_ptr() == q.data_ptr()) == (not strided and q.data_ptr() % 16 == 0)
