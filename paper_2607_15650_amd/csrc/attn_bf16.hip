@@ -865,11 +865,24 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_asm_kernel(const AttnArgs a)
         const int64_t rb0 = min(row0, a.q_len - 1);
         const __bf16* base = (const __bf16*)a.q + (int64_t)b * a.q_stride + rb0 * HD + (int64_t)h * D;
         const int last = (int)min((int64_t)(QB * 32 - 1), a.q_len - 1 - rb0);
+        if (((uintptr_t)a.q & 15) == 0) {
 #pragma unroll
-        for (int i = 0; i < C::QSTAGE / 1024; ++i) {
-          const int row = i * C::ROWS_PER_LOAD + ld_row;
-          lds_dma16(base, (uint32_t)min(row, last) * row_bytes + (uint32_t)((ld_unit ^ swz_k<D>(row)) * 16),
-                    smem_lds + qstage + (uint32_t)(i * 1024));
+          for (int i = 0; i < C::QSTAGE / 1024; ++i) {
+            const int row = i * C::ROWS_PER_LOAD + ld_row;
+            lds_dma16(base, (uint32_t)min(row, last) * row_bytes + (uint32_t)((ld_unit ^ swz_k<D>(row)) * 16),
+                      smem_lds + qstage + (uint32_t)(i * 1024));
+          }
+        } else {
+          // rows that are not 16-byte aligned go through registers: the
+          // direct loads into LDS do not read them in place
+#pragma unroll 1
+          for (int i = 0; i < C::QSTAGE / 1024; ++i) {
+            const int row = i * C::ROWS_PER_LOAD + ld_row;
+            const char* src = (const char*)base + ((uint32_t)min(row, last) * row_bytes + (uint32_t)((ld_unit ^ swz_k<D>(row)) * 16));
+            u32x4 x;
+            __builtin_memcpy(&x, __builtin_assume_aligned(src, 2), 16);
+            *(u32x4*)(smem + qstage + i * 1024 + lane * 16) = x;
+          }
         }
       }
       if constexpr (D == 128) {

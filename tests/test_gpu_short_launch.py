@@ -95,3 +95,27 @@ def test_step_takes_a_strided_query_tensor():
         sa = SelectiveAttention(2, 2, 64, [0, 200, 400, 600], 0.125)
         res.append(sa.step(0, 1, x, k, v, [1, 1, 1]))
     assert all(torch.equal(a, b) for a, b in zip(*res))
+
+
+@pytest.mark.parametrize("D,H,q_len", [(64, 3, 300), (128, 3, 300), (64, 12, 2048)])
+@pytest.mark.parametrize("shift", [1, 2, 4])
+def test_query_tensor_at_any_even_address(D, H, q_len, shift):
+    """bf16 queries 2, 4 or 8 bytes past a 16-byte boundary: the launch on an
+    aligned copy, bit for bit, through the call and through an engine."""
+    import torch
+    from paper_2607_15650_amd import api
+    from paper_2607_15650_amd.step import SelectiveAttention
+    offs = [0, q_len, 2 * q_len]
+    g = torch.Generator(device="cuda").manual_seed(shift)
+    flat = torch.randn(2 * 2 * q_len * H * D + 8, generator=g, device="cuda").to(torch.bfloat16)
+    q = flat[shift:shift + 4 * q_len * H * D].view(2, 2 * q_len, H, D)
+    k, v = (torch.randn((2, 2 * q_len, H, D), generator=g, device="cuda").to(torch.bfloat16) for _ in range(2))
+    assert q.data_ptr() % 16 != 0
+    res = []
+    for x in (q.clone(), q):
+        out = torch.full((2, 2, 2 * q_len, H, D), 9.0, dtype=torch.bfloat16, device="cuda")
+        lse = torch.full((2, 2, H, 2 * q_len), 9.0, device="cuda")
+        api.attn_partition_states(x, k, v, offs, [1, 1], D ** -0.5, out, lse)
+        sa = SelectiveAttention(2, H, D, offs, D ** -0.5)
+        res.append((out, lse) + sa.step(0, 1, x, k, v, [1, 1]))
+    assert all(torch.equal(a, b) for a, b in zip(*res))
