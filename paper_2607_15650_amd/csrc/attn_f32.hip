@@ -9,19 +9,32 @@
 // Products
 //   The float32 MFMA runs at a sixteenth of the bf16 one.  Every float32
 //   operand x is split into three bf16 planes, x = x1 + x2 + x3 (each the
-//   rounding of what the planes before it leave: exact, 3 x 8 bits), and a
+//   rounding of what the planes before it leave: 3 x 8 bits, exact), and a
 //   product is the sum of six bf16 MFMAs with float32 accumulation,
 //     x3 y1 + x2 y2 + x1 y3 + x2 y1 + x1 y2 + x1 y1,
-//   6/16 of the float32 MFMA's time.  The three products left out are of the
-//   order of 2^-26 |x y|, below the rounding of one float32 product, and
-//   there are fewer accumulations: against 64 bits, OUT is off by
+//   6/16 of the float32 MFMA's time.  The three products left out come to at
+//   most 2^-24 |x y| (two of 2^-8 x 2^-17; the rounding of one float32
+//   product) and to 2^-27 ... 2^-26.5 as a root mean square, and there are
+//   fewer accumulations: against 64 bits, OUT is off by
 //   2e-7 ... 7e-7 (norm ratio, 1,000 ... 2,000 keys) where the float32 MFMA's
 //   was off by 5e-7 ... 9e-7; LSE is the same.  The scores' five small terms
 //   have an accumulator of their own.
-//   A value that is not finite, or rounds to infinity in bf16, gives NaN in
-//   the planes, and so does every row it enters: a workgroup in which some
-//   row's sum or output ends up not finite runs its task again with the
-//   float32 MFMA, which treats infinities as float32 arithmetic does.
+//   What the planes cannot hold goes through the float32 MFMA: a workgroup
+//   runs its task again with it
+//    - where some row's sum or output ends up not finite.  A value that is not
+//      finite, or rounds to infinity in bf16, gives NaN in the planes and in
+//      every row it enters; the float32 MFMA treats infinities as float32
+//      arithmetic does;
+//    - where nonzero values below 2^-110 matter.  Their third plane falls
+//      under bf16's smallest subnormal (2^-133), so such a value is off by up
+//      to 2^-134.  Its queries are looked at as they are split: one of these
+//      values, or one so large (2^100 after scaling) that what a key of this
+//      kind is off by would show in the scores (below it: 2^-27 at most).  In
+//      V the error is under 2^-34 of an output of 2^-100 or more, so V is
+//      looked through only where some output is smaller or zero (a column of
+//      zeros in V: 7,750 keys in the 128-row form 670 -> 753 us; 2,000 keys
+//      and 24 heads in the 256-row form 890 -> 938).
+//   Probabilities under 2^-110 are off by 2^-134 too: OUT by 2^-134 max|v|.
 //
 // Work decomposition
 //   A workgroup has RW x KW waves and 32 * RW query rows of one (partition,
@@ -77,6 +90,12 @@ __device__ __forceinline__ Planes split8(f32x8 x) {
   return r;
 }
 
+// 2^-110: nonzero values below it are not exact in the planes
+constexpr uint32_t kPlanesMin = 0x08800000u;
+__device__ __forceinline__ bool below_planes(float x) {
+  return (__float_as_uint(x) & 0x7fffffffu) - 1u < kPlanesMin - 1u;
+}
+
 // the six plane products, smallest first
 constexpr int kTerms = 6;
 constexpr int kTermA[kTerms] = {2, 1, 0, 1, 0, 0};
@@ -111,11 +130,12 @@ struct CfgF {
 // One pass over this wave's (KW > 1) or workgroup's (KW = 1) key tiles
 // [t0, t1): unnormalised O^T, row maximum m (base 2, scaled) and the lane's
 // half of the row sum.  SPLIT: bf16 planes, otherwise the float32 MFMA.
+// `ask`: the lanes whose query values need the latter.
 template <class C, bool SPLIT>
 __device__ __forceinline__ void key_loop(const float* __restrict__ qrow, bool row_ok, const float* __restrict__ kg,
                                          const float* __restrict__ vg, int64_t HD, int kv_len, int t0, int t1,
                                          float sl2, unsigned char* buf, int gt, f32x16 (&o)[C::DB],
-                                         float& m, float& l) {
+                                         float& m, float& l, uint64_t& ask) {
   constexpr int D = C::D;
   const int lane = threadIdx.x & 63;
   const int lr = lane & 31;
@@ -138,6 +158,15 @@ __device__ __forceinline__ void key_loop(const float* __restrict__ qrow, bool ro
         x[e] = row_ok ? x0[e] : 0.f;
         x[4 + e] = row_ok ? x1[e] : 0.f;
       }
+      // smallest nonzero and largest magnitude (as bits; 0 - 1 is the largest)
+      uint32_t lo = ~0u, hi = 0;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const uint32_t u = __float_as_uint(x[e]) & 0x7fffffffu;
+        lo = min(lo, u - 1u);
+        hi = max(hi, u);
+      }
+      ask |= __builtin_amdgcn_ballot_w64(lo < kPlanesMin - 1u || __uint_as_float(hi) * sl2 >= 0x1p100f);
       qp[s] = split8(x);
     }
   } else {
@@ -425,23 +454,53 @@ __global__ __launch_bounds__(C::NT, C::WPE) void attn_f32_kernel(const AttnArgs 
   const int gt = C::KW == 1 ? tid : lane;
   float* part_m = (float*)(smem + C::KW * C::GROUP);         // [KW][32] maximum, then [KW][32] row sum
   float* part_l = part_m + C::KW * 32;
+  // run the task again; look through V; V asks for it (a word each: a wave may
+  // still be reading one when another writes the next)
   int* redo = (int*)(part_l + C::KW * 32);
 
   f32x16 o[C::DB];
   float m, l;
-  if (tid == 0) *redo = 0;
-  key_loop<C, true>(qrow, row_ok, kg, vg, HD, kv_len, t0, t1, a.scale_log2, kb, gt, o, m, l);
+  if (tid < 3) redo[tid] = 0;
+  uint64_t ask = 0;
+  key_loop<C, true>(qrow, row_ok, kg, vg, HD, kv_len, t0, t1, a.scale_log2, kb, gt, o, m, l, ask);
   // sum of 0 * x: NaN where a value is not finite
-  float bad = l * 0.f;
+  float bad = l * 0.f, low = INFINITY;
 #pragma unroll
   for (int db = 0; db < C::DB; ++db)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) bad = __builtin_fmaf(o[db][r], 0.f, bad);
+    for (int r = 0; r < 16; ++r) {
+      bad = __builtin_fmaf(o[db][r], 0.f, bad);
+      low = fminf(low, fabsf(o[db][r]));
+    }
+  const float below = pair_sum(l) * 0x1p-100f;
+  const bool small = row_ok && low < below;
   __syncthreads();
-  if (__builtin_amdgcn_ballot_w64(!(bad == 0.f)) != 0 && lane == 0) *redo = 1;
+  if ((__builtin_amdgcn_ballot_w64(!(bad == 0.f)) | ask) != 0 && lane == 0) redo[0] = 1;
+  if (__builtin_amdgcn_ballot_w64(small) != 0 && lane == 0) redo[1] = 1;
   __syncthreads();
-  if (__builtin_amdgcn_readfirstlane(*redo) != 0) {
-    key_loop<C, false>(qrow, row_ok, kg, vg, HD, kv_len, t0, t1, a.scale_log2, kb, gt, o, m, l);
+  bool again = __builtin_amdgcn_readfirstlane(redo[0]) != 0;
+  if (!again && __builtin_amdgcn_readfirstlane(redo[1]) != 0) {
+    constexpr int kBatch = 8;                                // loads in flight
+    const int64_t units = (int64_t)kv_len * (D / 4);
+    bool found = false;
+    for (int64_t i0 = tid; i0 < units; i0 += kBatch * C::NT) {
+      f32x4 x[kBatch];
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i) {
+        const int64_t u = min(i0 + i * C::NT, units - 1);
+        x[i] = *(const f32x4*)(vg + u / (D / 4) * HD + u % (D / 4) * 4);
+      }
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) found |= below_planes(x[i][e]);
+    }
+    if (__builtin_amdgcn_ballot_w64(found) != 0 && lane == 0) redo[2] = 1;
+    __syncthreads();
+    again = __builtin_amdgcn_readfirstlane(redo[2]) != 0;
+  }
+  if (again) {
+    key_loop<C, false>(qrow, row_ok, kg, vg, HD, kv_len, t0, t1, a.scale_log2, kb, gt, o, m, l, ask);
     __syncthreads();
   }
 

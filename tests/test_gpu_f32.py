@@ -106,3 +106,41 @@ def test_operands_the_planes_cannot_hold(D, H, q_len):
     assert bool(torch.isnan(out[3][0, :, 0]).all())
     if H > 1:
         assert float((out[3][0, :, 1:] - outs[3][0, :, 1:]).abs().max()) <= 1e-5
+
+
+@pytest.mark.parametrize("D,H,q_len", [(64, 1, 40), (64, 20, 260), (128, 1, 40), (128, 60, 129), (128, 120, 257)])
+def test_values_below_the_range_of_the_planes(D, H, q_len):
+    """Nonzero operands under 2^-110 have fewer bits in the planes than in
+    float32: V columns of ever smaller values, down to float32's subnormal
+    ones, beside a column of zeros, and queries so small that only large keys
+    make scores of them.
+
+    Tolerance: 1e-5 of the column's largest output, and where products are
+    subnormal half a spacing (2^-150) for each of the n terms, the sum and its
+    normalisation."""
+    import torch
+    lens = [70, 33]
+    offs = [0, 70, 103]
+    scale = 1 / math.sqrt(D)
+    q, k, v = inputs(1, q_len, offs[-1], H, D, 5)
+    for i, e in enumerate((0, 100, 109, 111, 113, 116, 120, 124, 126, 128, 132, 136, 140)):
+        v[:, :, 0, i] *= 2.0 ** -e
+    v[:, :, 0, 20] = 0.0
+    v[:, :70, 0, 21] = 0.0
+    v[0, 50, 0, 21] = 2.0 ** -140
+    if H > 1:                                    # a head of zeros, and one of ordinary values
+        v[:, :, 1] = 0.0
+    out, lse = run(q, k, v, offs, scale)
+    outs, lses = reference(q, k, v, offs, scale)
+    for j, n in enumerate(lens):
+        tol = 1e-5 * outs[j].abs().amax(1, keepdim=True) + (n + 2) * 2.0 ** -150
+        bad = ((out[j] - outs[j]).abs() > tol).nonzero()
+        assert len(bad) == 0, (j, bad[0].tolist(), len(bad))
+        assert float((lse[j] - lses[j]).abs().max()) <= 1e-5, j
+    for e in (115, 125):
+        ks, qs = k * 2.0 ** e, q * 2.0 ** -e     # the same scores, but for subnormal queries
+        out, lse = run(qs, ks, v, offs, scale)
+        outs, lses = reference(qs, ks, v, offs, scale)
+        for j in range(2):
+            assert float((out[j] - outs[j]).abs().max()) <= 1e-5, (e, j)
+            assert float((lse[j] - lses[j]).abs().max()) <= 1e-5, (e, j)
