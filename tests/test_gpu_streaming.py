@@ -209,3 +209,13 @@ def test_first_composition_inside_a_capture(grouped):
         torch.cuda.synchronize()
         assert torch.equal(w, ref), i
         assert torch.equal(step(2 + i), ref), i
+
+
+def test_calls_go_to_the_current_stream():
+    import torch
+    from paper_2607_15650_amd import api
+    assert api._stream() == torch.cuda.current_stream().cuda_stream
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        assert api._stream() == s.cuda_stream
+    assert api._stream() == torch.cuda.current_stream().cuda_stream != s.cuda_stream
