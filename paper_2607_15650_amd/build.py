@@ -16,12 +16,13 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libditango.so")
-SOURCES = ["ditango_api.cpp", "attn_bf16.hip", "attn_f32.hip", "merge.hip", "norms.hip", "probe.hip"]
+SOURCES = ["ditango_api.cpp", "attn_bf16.hip", "attn_bf16_any_q.hip", "attn_f32.hip", "merge.hip", "norms.hip", "probe.hip"]
 ARCH = "gfx950"
 # Per-source compiler options.  The attention kernel is scheduled with the
 # backend's iterative ILP strategy, which interleaves its MFMAs, LDS reads and
 # softmax VALU work better than the default (2-4 % faster on both head dims).
-SOURCE_FLAGS = {"attn_bf16.hip": ["-mllvm", "--amdgpu-sched-strategy=iterative-ilp"]}
+_ILP = ["-mllvm", "--amdgpu-sched-strategy=iterative-ilp"]
+SOURCE_FLAGS = {"attn_bf16.hip": _ILP, "attn_bf16_any_q.hip": _ILP}
 
 
 def hipcc() -> str:
@@ -46,6 +47,7 @@ def flags():
 
 # what a source includes besides internal.h: shared and generated code
 INCLUDES = {"attn_bf16.hip": ["attn_tile.h", "attn_d128_loop.inc", "attn_d64_loop.inc"],
+            "attn_bf16_any_q.hip": ["attn_bf16.hip", "attn_tile.h", "attn_d128_loop.inc", "attn_d64_loop.inc"],
             "attn_f32.hip": ["attn_tile.h"]}
 
 

@@ -752,7 +752,10 @@ __device__ __forceinline__ u32x4 raw_buffer_desc(const void* base, uint32_t nbyt
                (uint32_t)__builtin_amdgcn_readfirstlane(nbytes), 0x00020000u};
 }
 
-template <int D_, typename TS>
+// QA: the query rows are 16-byte aligned (a test of it in front of their loads
+// cost short launches 1-2 %: 8 partitions of 2,048 keys, 2,048 rows x 12 heads
+// at D=64 106.5 -> 108.4 us).
+template <int D_, typename TS, bool QA>
 __global__ __launch_bounds__(256, 1) void attn_bf16_asm_kernel(const AttnArgs a) {
   using C = AsmCfg<D_>;
   constexpr int D = C::D, QB = C::QB, BN = C::BN, KS = C::KS, DB = C::DB, LW = C::LW;
@@ -865,7 +868,7 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_asm_kernel(const AttnArgs a)
         const int64_t rb0 = min(row0, a.q_len - 1);
         const __bf16* base = (const __bf16*)a.q + (int64_t)b * a.q_stride + rb0 * HD + (int64_t)h * D;
         const int last = (int)min((int64_t)(QB * 32 - 1), a.q_len - 1 - rb0);
-        if (((uintptr_t)a.q & 15) == 0) {
+        if constexpr (QA) {
 #pragma unroll
           for (int i = 0; i < C::QSTAGE / 1024; ++i) {
             const int row = i * C::ROWS_PER_LOAD + ld_row;
@@ -1139,14 +1142,14 @@ struct CompiledKernel {
   }
 };
 
-template <int D, typename TS>
+template <int D, typename TS, bool QA>
 struct AsmKernel {
   using C = AsmCfg<D>;
   static constexpr int Dim = D, NT = C::NT, BM = C::BM, KEYS = C::BN;
   static constexpr size_t LDS = C::LDS_BYTES;
-  static const void* fn() { return (const void*)attn_bf16_asm_kernel<D, TS>; }
+  static const void* fn() { return (const void*)attn_bf16_asm_kernel<D, TS, QA>; }
   static void launch(dim3 grid, hipStream_t s, const AttnArgs& a) {
-    hipLaunchKernelGGL((attn_bf16_asm_kernel<D, TS>), grid, dim3(NT), LDS, s, a);
+    hipLaunchKernelGGL((attn_bf16_asm_kernel<D, TS, QA>), grid, dim3(NT), LDS, s, a);
   }
 };
 
@@ -1263,6 +1266,8 @@ hipError_t launch_cfg(const AttnArgs& a0, void* ws, size_t ws_bytes, hipStream_t
   return hipGetLastError();
 }
 
+#ifndef DITANGO_ANY_Q
+
 // The hand-scheduled loops bound their tile loads with 32-bit buffer
 // descriptors: every selected partition's bytes for one head must stay
 // below 2^31.
@@ -1324,13 +1329,19 @@ inline bool d64_use_asm(const AttnArgs& a) {
 #define DITANGO_ASM 1
 #endif
 
+template <int D, typename TS>
+static hipError_t launch_asm(const AttnArgs& a, void* ws, size_t ws_bytes, hipStream_t s) {
+  // rows are multiples of 128 bytes: all of them lie as the first one does
+  if (((uintptr_t)a.q & 15) == 0) return launch_cfg<AsmKernel<D, TS, true>, TS>(a, ws, ws_bytes, s);
+  return launch_attn_asm_any_q(a, D, sizeof(TS) == 4, ws, ws_bytes, s);
+}
+
 hipError_t launch_attn_bf16_ws(const AttnArgs& a, int D, bool state_f32, void* ws, size_t ws_bytes,
                                hipStream_t s) {
   if (D == 128) {
 #if DITANGO_ASM
     if (asm_fits(a, 128))
-      return state_f32 ? launch_cfg<AsmKernel<128, float>, float>(a, ws, ws_bytes, s)
-                       : launch_cfg<AsmKernel<128, __bf16>, __bf16>(a, ws, ws_bytes, s);
+      return state_f32 ? launch_asm<128, float>(a, ws, ws_bytes, s) : launch_asm<128, __bf16>(a, ws, ws_bytes, s);
 #endif
     return state_f32 ? launch_cfg<CompiledKernel<128, DITANGO_D128_CFG, float>, float>(a, ws, ws_bytes, s)
                      : launch_cfg<CompiledKernel<128, DITANGO_D128_CFG, __bf16>, __bf16>(a, ws, ws_bytes, s);
@@ -1338,8 +1349,7 @@ hipError_t launch_attn_bf16_ws(const AttnArgs& a, int D, bool state_f32, void* w
   if (D == 64) {
 #if DITANGO_ASM
     if (d64_use_asm(a))
-      return state_f32 ? launch_cfg<AsmKernel<64, float>, float>(a, ws, ws_bytes, s)
-                       : launch_cfg<AsmKernel<64, __bf16>, __bf16>(a, ws, ws_bytes, s);
+      return state_f32 ? launch_asm<64, float>(a, ws, ws_bytes, s) : launch_asm<64, __bf16>(a, ws, ws_bytes, s);
 #endif
     return state_f32 ? launch_cfg<CompiledKernel<64, DITANGO_D64_CFG, float>, float>(a, ws, ws_bytes, s)
                      : launch_cfg<CompiledKernel<64, DITANGO_D64_CFG, __bf16>, __bf16>(a, ws, ws_bytes, s);
@@ -1359,9 +1369,9 @@ hipError_t attn_bf16_ws_bytes(const AttnArgs& a, int D, size_t* bytes) {
   hipError_t e = hipErrorInvalidValue;
 #if DITANGO_ASM
   if (D == 128 && asm_fits(a, 128))
-    e = plan_cfg<AsmKernel<128, __bf16>>(a, &p);
+    e = plan_cfg<AsmKernel<128, __bf16, true>>(a, &p);
   else if (D == 64 && d64_use_asm(a))
-    e = plan_cfg<AsmKernel<64, __bf16>>(a, &p);
+    e = plan_cfg<AsmKernel<64, __bf16, true>>(a, &p);
   else
 #endif
   if (D == 128)
@@ -1371,5 +1381,19 @@ hipError_t attn_bf16_ws_bytes(const AttnArgs& a, int D, size_t* bytes) {
   if (e == hipSuccess) *bytes = p.bytes;
   return e;
 }
+
+#else  // DITANGO_ANY_Q
+
+}  // namespace
+
+hipError_t launch_attn_asm_any_q(const AttnArgs& a, int D, bool state_f32, void* ws, size_t ws_bytes, hipStream_t s) {
+  if (D == 128)
+    return state_f32 ? launch_cfg<AsmKernel<128, float, false>, float>(a, ws, ws_bytes, s)
+                     : launch_cfg<AsmKernel<128, __bf16, false>, __bf16>(a, ws, ws_bytes, s);
+  return state_f32 ? launch_cfg<AsmKernel<64, float, false>, float>(a, ws, ws_bytes, s)
+                   : launch_cfg<AsmKernel<64, __bf16, false>, __bf16>(a, ws, ws_bytes, s);
+}
+
+#endif  // DITANGO_ANY_Q
 
 }  // namespace ditango

@@ -172,6 +172,10 @@ hipError_t attn_bf16_ws_bytes(const AttnArgs& a, int D, size_t* bytes);
 // attn_bf16_ws_bytes; a null workspace runs the static assignment.
 hipError_t launch_attn_bf16_ws(const AttnArgs& a, int D, bool state_f32, void* ws, size_t ws_bytes,
                                hipStream_t s);
+// launch_attn_bf16_ws of the hand-scheduled kernel for queries at any even
+// address.
+hipError_t launch_attn_asm_any_q(const AttnArgs& a, int D, bool state_f32, void* ws, size_t ws_bytes,
+                                 hipStream_t s);
 hipError_t launch_attn_f32(const AttnArgs& a, int D, hipStream_t s);
 hipError_t launch_merge(const MergeArgs& a, ditango_dtype sdt, ditango_dtype odt, int D,
                         hipStream_t s);
