@@ -130,9 +130,11 @@ def attn_mode(ws):
 
 def attn_kernels(ws, w, select):
     """The kernels of one attention launch: the hand-scheduled kernel, except
-    in D=64 launches of partitions of unequal lengths or whose 384-row tasks
-    fit one round (d64_use_asm in attn_bf16.hip); the queue counters serve
-    launches of at least eight rounds, or of unequal partitions."""
+    in D=64 launches of which one round holds the 384-row tasks and not the
+    256-row ones (d64_use_asm in attn_bf16.hip: of those it runs the ones whose
+    last round is split, with partitions of 32 tiles or more); the queue
+    counters serve launches of at least eight rounds, or of unequal
+    partitions."""
     import torch
     mode = attn_mode(ws)
     cus = torch.cuda.get_device_properties(0).multi_processor_count
@@ -141,7 +143,8 @@ def attn_kernels(ws, w, select):
     lens = [w.offsets[j + 1] - w.offsets[j] for j in select]
     equal = 8 * (max(lens) - min(lens)) <= max(lens)
     one_round = -(-w.q_len // 384) * heads <= cus
-    asm = w.D == 128 or tasks >= 4 * cus or (equal and not (one_round and 8 * tasks >= 11 * cus))
+    asm = w.D == 128 or tasks <= cus or not one_round or \
+        (mode == "split" and 8 * tasks < 11 * cus and -(-max(lens) // 64) >= 32)
     k = f"attn_bf16_asm_kernel<{w.D}>" if asm else f"attn_bf16_kernel<{w.D}>"
     reset = "attn_queue_reset_kernel + " if tasks >= 8 * cus or not equal else ""
     return {"static": k, "queue": reset + k, "split": f"{reset}{k} + attn_split_fixup_kernel"}[mode]

@@ -1278,33 +1278,45 @@ inline bool asm_fits(const AttnArgs& a, int D) {
   return true;
 }
 
-// Which D=64 kernel a launch runs: the hand-scheduled one (256 rows per task)
-// from four rounds on, and in shorter launches of equal partitions (one card,
-// static / with the workspace, compiled kernel against this one: 2,048 rows x
-// 12 heads, 3 partitions of 2,048 keys 62.6 / 65.4 against 66.7 / 55.8 us, 1
-// partition 50.0 / 37.3 against 29.6, 8 partitions 163.8 / 153.6 against
-// 104.5; 1,639 x 3, 6 partitions 42.1 / 39.1 against 28.2; 1,000 x 40, 5
-// partitions 96.6 / 101.6 against 81.7 / 80.6), with two exceptions:
-//  - the compiled kernel's 384-row tasks fit one round of which 256-row tasks
-//    would make about one and a half: 6,144 x 8, 2 partitions of 2,048 keys
-//    64.0 against 65.9 us, 1,536 x 20, 3 of 2,048 59.6 against 61.0, 3,072 x
-//    8, 4 of 512 23.9 against 24.7;
-//  - partitions of unequal lengths, which stay with the compiled kernel and
-//    the split tail that goes with its 384-row tasks (6,244 x 8, 700 and
-//    1,234 keys: 54.1 us split, 48.9 here; 9,000 x 6, 700 and 400 keys: 47.6
-//    against 33.3).
-inline bool d64_use_asm(const AttnArgs& a) {
+// Which D=64 kernel a launch with `ws_bytes` of workspace runs: the
+// hand-scheduled one (256 rows per task), but for launches of which one round
+// holds the compiled kernel's 384-row tasks and not the 256-row ones.  Outside
+// that range the compiled kernel is behind (us without / with a workspace,
+// compiled against hand-scheduled, one card): 6,244 rows x 8 heads, partitions
+// of 700 and 1,234 keys 65.0 / 49.1 against 44.2 / 46.0; 9,000 x 6, 700 and 400
+// 48.0 / 47.4 against 30.8 / 33.6; 2,048 x 12, 2,048 and 1,024 48.6 / 49.4
+// against 30.7 / 30.1; 5,000 x 10, 3,000 and 300 143 / 90.6 against 86.3 / 80.3;
+// 2,048 x 12, 1 of 2,048 48.0 / 48.9 against 29.1 / 28.9, 8 of 2,048 160 / 140
+// against 112 / 108; 1,000 x 40, 5 of 1,000 92.4 / 92.5 against 81.6 / 79.5.
+//
+// Within it the compiled kernel is ahead: 4,196 x 8, 2 of 1,234 33.2 / 33.3
+// against 42.4 / 36.0, 700 and 1,234 36.0 / 33.9 against 43.6 / 35.6; 4,096 x 9,
+// 2 of 1,024 30.4 / 30.3 against 35.4 / 37.2; 1,100 x 19, 3 of 900 28.0 / 28.2
+// against 34.5 / 33.2; 1,300 x 11, 5 of 1,300 36.9 / 37.3 against 44.2 / 42.2;
+// 6,144 x 8, 2 of 2,048 64.0 / 60.0 against 66.0 / 64.0; except that long
+// partitions make the split of the last round pay (kLongTiles), given the
+// workspace for it and less than 1 3/8 rounds: 2,048 x 12, 3 of 2,048 58.3 /
+// 53.8 against 62.2 / 50.5; 4,900 x 7, 2 of 2,000 48.5 / 48.3 against 61.5 /
+// 50.0, 600 and 2,000 47.9 / 50.3 against 62.3 / 43.9; 2,100 x 12, 3 of 2,730
+// 67.1 / 66.7 against 79.6 / 66.9; 4,096 x 9, 2 of 4,096 93.0 / 91.6 against 112
+// / 82.4; 4,196 x 8, 2 of 12,000 240 / 240 against 310 / 203.
+constexpr int kLongTiles = 32;
+inline bool d64_use_asm(const AttnArgs& a, size_t ws_bytes) {
   if (!asm_fits(a, 64)) return false;
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
       cus <= 0)
     return false;
-  const int64_t heads = (int64_t)a.H * a.B * a.n_sel;
-  const int64_t tasks = (a.q_len + AsmCfg<64>::BM - 1) / AsmCfg<64>::BM * heads;
-  if (tasks >= 4 * (int64_t)cus) return true;
+  using C = AsmCfg<64>;
   constexpr int kCompiledRows = 384;
-  const bool one_round = (a.q_len + kCompiledRows - 1) / kCompiledRows * heads <= cus;
-  return equal_lengths(a) && !(one_round && 8 * tasks >= 11 * (int64_t)cus);
+  const int64_t heads = (int64_t)a.H * a.B * a.n_sel;
+  const int64_t tasks = (a.q_len + C::BM - 1) / C::BM * heads;
+  if (tasks <= cus || (a.q_len + kCompiledRows - 1) / kCompiledRows * heads > cus) return true;
+  int32_t longest = 0;
+  for (int j = 0; j < a.n_sel; ++j) longest = a.kv_len[j] > longest ? a.kv_len[j] : longest;
+  if (8 * tasks >= 11 * (int64_t)cus || (longest + C::BN - 1) / C::BN < kLongTiles) return false;
+  Plan p;
+  return plan_cfg<AsmKernel<64, __bf16, true>>(a, &p) == hipSuccess && p.f > 1 && ws_bytes >= p.bytes;
 }
 
 }  // namespace
@@ -1348,7 +1360,7 @@ hipError_t launch_attn_bf16_ws(const AttnArgs& a, int D, bool state_f32, void* w
   }
   if (D == 64) {
 #if DITANGO_ASM
-    if (d64_use_asm(a))
+    if (d64_use_asm(a, ws != nullptr ? ws_bytes : 0))
       return state_f32 ? launch_asm<64, float>(a, ws, ws_bytes, s) : launch_asm<64, __bf16>(a, ws, ws_bytes, s);
 #endif
     return state_f32 ? launch_cfg<CompiledKernel<64, DITANGO_D64_CFG, float>, float>(a, ws, ws_bytes, s)
@@ -1370,7 +1382,7 @@ hipError_t attn_bf16_ws_bytes(const AttnArgs& a, int D, size_t* bytes) {
 #if DITANGO_ASM
   if (D == 128 && asm_fits(a, 128))
     e = plan_cfg<AsmKernel<128, __bf16, true>>(a, &p);
-  else if (D == 64 && d64_use_asm(a))
+  else if (D == 64 && d64_use_asm(a, SIZE_MAX))
     e = plan_cfg<AsmKernel<64, __bf16, true>>(a, &p);
   else
 #endif

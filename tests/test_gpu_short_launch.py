@@ -20,6 +20,13 @@ CASES = [
     (128, 3, 257, [65, 64, 63]),
     (64, 12, 3800, [70, 64, 66, 65, 64, 63, 64, 64, 70, 68, 64, 66]),   # 2,160 tasks: claimed
     (128, 12, 3800, [70, 64, 66, 65, 64, 63, 64, 64, 70, 68, 64, 66]),
+    # D=64 around one round of 384-row tasks on 256 compute units
+    (64, 9, 4096, [1024, 1000]),                   # 198 of them, 288 of 256 rows, short partitions: compiled kernel
+    (64, 12, 2048, [2048, 2000, 2048]),            # 216, 288, long: compiled, or split with the workspace for it
+    (64, 9, 4096, [300, 2100]),                    # the same of unequal lengths
+    (64, 8, 6244, [700, 1234]),                    # 272: hand-scheduled
+    (64, 8, 6244, [700, 2500]),                    # its last round split
+    (64, 12, 2048, [2048, 700]),                   # 192 of 256 rows: hand-scheduled
 ]
 
 
@@ -57,6 +64,56 @@ def test_launches_match_static_and_float64(D, H, q_len, lens):
             for out, l in (static, full):
                 assert float((out[j, 0, :, h].double() - ref).abs().max()) <= tol, (j, h)
                 assert float((l[j, 0, h].double() - lse).abs().max()) <= 2e-3, (j, h)
+
+
+def split_bytes(n, f):
+    """Workspace of a split of n tasks of 256 rows at D=64 over f key ranges."""
+    up = lambda x: -(-x // 256) * 256
+    return 256 + up(n * f * 256 * 64 * 4) + up(n * f * 256 * 4)
+
+
+@pytest.mark.parametrize("H,q_len,lens,split", [
+    (9, 4096, [1024, 1024], None),                 # one round of 384-row tasks, short partitions
+    (9, 4096, [300, 1984], None),                  # 31 tiles
+    (9, 4096, [300, 1985], (32, 8)),               # 32: 256-row tasks, 288 of them
+    (12, 2048, [2048, 2048, 2048], (32, 8)),
+    (8, 6144, [2048, 2048], None),                 # 384 of them: a round and a half
+    (8, 6244, [700, 2500], (144, 3)),              # 272 of 384 rows
+    (12, 2048, [2048, 700], None),                 # 192 of 256 rows: nothing to split
+])
+def test_plan_of_short_head_dim_64_launches(H, q_len, lens, split):
+    """The workspace tells which kernel's tasks a launch runs."""
+    import torch
+    from paper_2607_15650_amd import api
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("shapes are for 256 compute units")
+    offs = [sum(lens[:j]) for j in range(len(lens) + 1)]
+    need = api.attn_workspace_bytes(torch.bfloat16, 1, H, 64, q_len, offs, [1] * len(lens))
+    assert need == (256 if split is None else split_bytes(*split))
+
+
+def test_compiled_kernel_splits_its_last_round():
+    """K of 2 GiB a partition, which the hand-scheduled kernel cannot address:
+    272 tasks of 384 rows, the last 16 split."""
+    import torch
+    from paper_2607_15650_amd import api
+    H, D, q_len, n = 272, 64, 100, 61700
+    g = torch.Generator(device="cuda").manual_seed(0)
+    q, k, v = (torch.randn((1, m, H, D), generator=g, device="cuda", dtype=torch.bfloat16) for m in (q_len, n, n))
+    need = api.attn_workspace_bytes(torch.bfloat16, 1, H, D, q_len, [0, n], [1])
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert need > 256
+    for size in (None, need):
+        out = torch.full((1, 1, q_len, H, D), 9.0, dtype=torch.bfloat16, device="cuda")
+        lse = torch.full((1, 1, H, q_len), 9.0, device="cuda")
+        ws = None if size is None else torch.full((size,), 0x5A, dtype=torch.uint8, device="cuda")
+        api.attn_partition_states(q, k, v, [0, n], [1], D ** -0.5, out, lse, ws)
+        for h in (0, 131, 255, 256, 271):
+            s = torch.mm(q[0, :, h].double(), k[0, :, h].double().t().contiguous()) * D ** -0.5
+            l = torch.logsumexp(s, 1)
+            ref = torch.mm((s - l[:, None]).exp(), v[0, :, h].double())
+            assert float((out[0, 0, :, h].double() - ref).abs().max()) <= 1e-2, h
+            assert float((lse[0, 0, h].double() - l).abs().max()) <= 2e-3, h
 
 
 @pytest.mark.parametrize("dtype,D,H", [("bf16", 64, 3), ("bf16", 128, 3), ("f32", 64, 3), ("f32", 128, 60)])

@@ -4,8 +4,8 @@ composed by a fix-up kernel.  Checked against the float64 oracle, against
 the unsplit launch, for determinism, and for leaving unselected slots alone.
 
 Shapes are chosen from the device's compute-unit count so that one full
-round plus 16 tasks is launched: the 16 tail tasks are split 7 or 8 ways,
-and the last key range of each ends in a partial tile.
+round (two at D=64) plus 16 tasks is launched: the 16 tail tasks are split 7
+or 8 ways, and the last key range of each ends in a partial tile.
 """
 import numpy as np
 import pytest
@@ -15,9 +15,11 @@ from helpers import TOL, exact_inputs, max_abs, new_state_cache, to_gpu
 
 pytestmark = pytest.mark.gpu
 
-# query rows per workgroup of the kernel each head dim's launches here run
-# (D=64 launches of fewer than four rounds run the compiled kernel)
-ROWS = {128: 256, 64: 384}
+# query rows per workgroup of the hand-scheduled kernel, which every launch
+# here runs, and the full rounds before the split one (at D=64 a launch whose
+# 384-row tasks fit one round may run the compiled kernel)
+ROWS = {128: 256, 64: 256}
+ROUNDS = {128: 1, 64: 2}
 
 
 def api():
@@ -42,7 +44,7 @@ def test_tail_split_matches_oracle_and_unsplit(D, lens, select, state_dt):
     H, B = 8, 1
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     per_tile = H * B * len(select)
-    q_tiles = (cus + 16 + per_tile - 1) // per_tile
+    q_tiles = (ROUNDS[D] * cus + 16 + per_tile - 1) // per_tile
     q_len = (q_tiles - 1) * ROWS[D] + 100
     offs = [0]
     for n in lens:
@@ -60,7 +62,7 @@ def test_tail_split_matches_oracle_and_unsplit(D, lens, select, state_dt):
     print(f"split case D={D} lens={lens} q_len={q_len} tasks={q_tiles * per_tile} cus={cus} ws={need}", flush=True)
     # more than the 256 bytes of queue counters: the plan asks for the
     # partial states of a split tail
-    assert need > 256, "one full round plus 16 tasks must split the tail"
+    assert need > 256, "full rounds plus 16 tasks must split the tail"
     ws = torch.empty(need, dtype=torch.uint8, device="cuda")
 
     sdt = torch.float32 if state_dt == "f32" else torch.bfloat16
