@@ -45,7 +45,7 @@ def flags():
     return CODEGEN_FLAGS + ["-I", INCLUDE, "-I", CSRC, "-Wall", "-Wno-unused-function"]
 
 
-# what a source includes besides internal.h: shared and generated code
+# what a source includes besides internal.h and what that includes: shared and generated code
 INCLUDES = {"attn_bf16.hip": ["attn_tile.h", "attn_d128_loop.inc", "attn_d64_loop.inc"],
             "attn_bf16_any_q.hip": ["attn_bf16.hip", "attn_tile.h", "attn_d128_loop.inc", "attn_d64_loop.inc"],
             "attn_f32.hip": ["attn_tile.h"]}
@@ -57,7 +57,8 @@ def source_id(name: str) -> str:
     from it can change."""
     import hashlib
     h = hashlib.sha256(open(os.path.join(CSRC, name), "rb").read())
-    h.update(open(os.path.join(CSRC, "internal.h"), "rb").read())
+    for inc in ("internal.h", "per_device.h"):
+        h.update(open(os.path.join(CSRC, inc), "rb").read())
     for inc in INCLUDES.get(name, []):
         h.update(open(os.path.join(CSRC, inc), "rb").read())
     h.update(" ".join(CODEGEN_FLAGS + SOURCE_FLAGS.get(name, [])).encode())

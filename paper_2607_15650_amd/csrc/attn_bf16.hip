@@ -1155,8 +1155,11 @@ struct AsmKernel {
 
 template <class K>
 hipError_t set_lds() {
-  static const hipError_t attr = hipFuncSetAttribute(K::fn(), hipFuncAttributeMaxDynamicSharedMemorySize, (int)K::LDS);
-  return attr;
+  static OncePerDevice once;
+  int dev = 0;
+  const hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  return once.run(dev, [] { return hipFuncSetAttribute(K::fn(), hipFuncAttributeMaxDynamicSharedMemorySize, (int)K::LDS); });
 }
 
 template <class K>

@@ -570,9 +570,11 @@ __global__ __launch_bounds__(C::NT, C::WPE) void attn_f32_kernel(const AttnArgs 
 }
 
 template <class C>
-hipError_t launch_cfg_f(const AttnArgs& a0, hipStream_t s) {
-  static const hipError_t attr =
-      hipFuncSetAttribute((const void*)attn_f32_kernel<C>, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
+hipError_t launch_cfg_f(const AttnArgs& a0, int dev, hipStream_t s) {
+  static OncePerDevice once;
+  const hipError_t attr = once.run(dev, [] {
+    return hipFuncSetAttribute((const void*)attn_f32_kernel<C>, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
+  });
   if (attr != hipSuccess) return attr;
   AttnArgs a = a0;
   a.q_tiles = (int)((a.q_len + C::BM - 1) / C::BM);
@@ -607,9 +609,9 @@ hipError_t launch_f32(const AttnArgs& a, hipStream_t s) {
   if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return e;
   const int64_t tiles = (int64_t)a.H * a.B * a.n_sel;
-  if ((a.q_len + Split::BM - 1) / Split::BM * tiles <= 2 * (int64_t)cus) return launch_cfg_f<Split>(a, s);
-  if ((a.q_len + Mid::BM - 1) / Mid::BM * tiles <= cus) return launch_cfg_f<Mid>(a, s);
-  return launch_cfg_f<Shared>(a, s);
+  if ((a.q_len + Split::BM - 1) / Split::BM * tiles <= 2 * (int64_t)cus) return launch_cfg_f<Split>(a, dev, s);
+  if ((a.q_len + Mid::BM - 1) / Mid::BM * tiles <= cus) return launch_cfg_f<Mid>(a, dev, s);
+  return launch_cfg_f<Shared>(a, dev, s);
 }
 
 }  // namespace

@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "ditango.h"
+#include "per_device.h"
 
 namespace ditango {
 
