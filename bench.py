@@ -3,10 +3,12 @@
 
 One step = one pass of the whole hot path for one context-parallel rank's
 query block: fresh states of the selected key/value partitions
-(ditango_attn_partition_states), composition with the cached states of the
-others (ditango_merge_states), and contribution weights
-(ditango_contrib).  The state cache is filled from the previous step's
-tensors before timing; all inputs are resident in HBM when timing starts.
+(ditango_attn_partition_states), and composition with the cached states of
+the others together with the contribution weights (ditango_compose, the call
+SelectiveAttention.step makes; ditango_merge_states and ditango_contrib, its
+two halves as calls of their own, are timed beside it).  The state cache is
+filled from the previous step's tensors before timing; all inputs are resident
+in HBM when timing starts.
 
 Default workload: the video-DiT shape (Wan2.1-14B latent, 75,600 tokens,
 40 heads, head dim 128, 8 partitions of 9,450 tokens, query partition 3,
@@ -31,7 +33,7 @@ sys.path.insert(0, ROOT)
 METRIC = "selective-attn step time (ms) + effective TFLOP/s and % bf16 MFMA peak, 1 GPU"
 DEFAULT_WORKLOAD = "videodit_bf16_h40_d128_s75600_p8"
 PEAK_BF16_TFLOPS = 2500.0      # MI355X dense bf16 MFMA
-PEAK_F32_TFLOPS = 157.3        # MI355X fp32 MFMA / vector
+PEAK_F32_TFLOPS = PEAK_BF16_TFLOPS / 6    # float32 products are six bf16 ones (attn_f32.hip)
 PEAK_HBM_GBS = 8000.0          # MI355X HBM3E
 
 # HBM bytes per launch of the attention kernel at the default workload, from
@@ -72,7 +74,7 @@ def parse():
                     help="workspace of the attention launch: queue counters and tail-split partials (full), "
                          "the queue counters only (balanced, unsplit), or none (static launch)")
     ap.add_argument("--graph", action="store_true",
-                    help="time the step as one captured HIP graph (counter reset, attention, merge, weights) "
+                    help="time the step as one captured HIP graph (attention, composition with weights) "
                          "replayed --steps times; the per-kernel times stay eager")
     ap.add_argument("--no-selection-sweep", dest="selection_sweep", action="store_false",
                     help="skip the step-time-against-selected-fraction points")
@@ -527,7 +529,7 @@ def sweep_result(w, steps, warmup):
     out = torch.empty((w.B, L, w.H, w.D), dtype=torch.bfloat16, device="cuda")
     lse = torch.empty((w.B, w.H, L), dtype=torch.float32, device="cuda")
     wp = torch.empty(w.P, dtype=torch.float32, device="cuda")
-    ws = torch.empty(max(16, api.contrib_workspace_bytes(w.B, w.H, L, w.P)), dtype=torch.uint8, device="cuda")
+    ws = api.compose_workspace(w.B, w.H, L, w.P)
     api.attn_partition_states(qp, kp, vp, offs, [1] * w.P, w.scale, st, ls)
     del qp, kp, vp
     rows = []
@@ -538,8 +540,7 @@ def sweep_result(w, steps, warmup):
 
         def step():
             api.attn_partition_states(q, k, v, offs, mask, w.scale, st, ls, ws_k)
-            api.merge_states(st, ls, out, lse)
-            api.contrib(ls, lse, wp, ws)
+            api.compose(st, ls, out, lse, wp, ws)
         for _ in range(warmup):
             step()
         e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
@@ -556,8 +557,7 @@ def sweep_result(w, steps, warmup):
             ea.record()
             api.attn_partition_states(q, k, v, offs, mask, w.scale, st, ls, ws_k)
             eb.record()
-            api.merge_states(st, ls, out, lse)
-            api.contrib(ls, lse, wp, ws)
+            api.compose(st, ls, out, lse, wp, ws)
         torch.cuda.synchronize()
         attn_ms = sum(ea.elapsed_time(eb) for ea, eb in evs) / steps
         flops = algorithmic(w, sel)[0]
@@ -642,7 +642,9 @@ def main():
     out = torch.empty((w.B, q_len, w.H, w.D), dtype=dt, device="cuda")
     lse = torch.empty((w.B, w.H, q_len), dtype=torch.float32, device="cuda")
     w_part = torch.empty(w.P, dtype=torch.float32, device="cuda")
-    ws = torch.empty(max(16, api.contrib_workspace_bytes(w.B, w.H, q_len, w.P)), dtype=torch.uint8, device="cuda")
+    ws = api.compose_workspace(w.B, w.H, q_len, w.P)
+    ws_contrib = torch.empty(max(16, api.contrib_workspace_bytes(w.B, w.H, q_len, w.P)), dtype=torch.uint8,
+                             device="cuda")
     # workspace of the attention launch: queue counters that balance its
     # last tasks over the XCDs, and room to split the tasks of a partly
     # filled last round over key ranges (None: the static launch)
@@ -673,12 +675,9 @@ def main():
         api.attn_partition_states(q, k, v, offs, mask, w.scale, out_states, lse_states, ws_attn)
         if ev is not None:
             ev[1].record()
-        api.merge_states(out_states, lse_states, out, lse)
+        api.compose(out_states, lse_states, out, lse, w_part, ws)
         if ev is not None:
             ev[2].record()
-        api.contrib(lse_states, lse, w_part, ws)
-        if ev is not None:
-            ev[3].record()
 
     for _ in range(args.warmup):
         step()
@@ -706,14 +705,20 @@ def main():
     torch.cuda.synchronize()
     ms_per_step = start.elapsed_time(stop) / args.steps
 
-    # pass 2: per-kernel durations with events between the calls
-    evs = [[torch.cuda.Event(enable_timing=True) for _ in range(4)] for _ in range(args.steps)]
-    for i in range(args.steps):
-        step(evs[i])
+    # pass 2: the calls' durations with events between them; behind every
+    # step, the composition and the weights as calls of their own
+    evs = [[torch.cuda.Event(enable_timing=True) for _ in range(5)] for _ in range(args.steps)]
+    for ev in evs:
+        step(ev)
+        api.merge_states(out_states, lse_states, out, lse)
+        ev[3].record()
+        api.contrib(lse_states, lse, w_part, ws_contrib)
+        ev[4].record()
     torch.cuda.synchronize()
     t_attn = sorted(e[0].elapsed_time(e[1]) for e in evs)
-    t_merge = sorted(e[1].elapsed_time(e[2]) for e in evs)
-    t_contrib = sorted(e[2].elapsed_time(e[3]) for e in evs)
+    t_compose = sorted(e[1].elapsed_time(e[2]) for e in evs)
+    t_merge = sorted(e[2].elapsed_time(e[3]) for e in evs)
+    t_contrib = sorted(e[3].elapsed_time(e[4]) for e in evs)
     mean = lambda a: sum(a) / len(a)
     med = lambda a: a[len(a) // 2]
 
@@ -755,8 +760,7 @@ def main():
 
             def step_k():
                 api.attn_partition_states(q, k, v, offs, mask_k, w.scale, out_states, lse_states, ws_k)
-                api.merge_states(out_states, lse_states, out, lse)
-                api.contrib(lse_states, lse, w_part, ws)
+                api.compose(out_states, lse_states, out, lse, w_part, ws)
             step_k()
             torch.cuda.synchronize()
             e0 = torch.cuda.Event(enable_timing=True)
@@ -835,6 +839,7 @@ def main():
                      "traffic": attn_traffic(w, select, attn_mode(ws_attn)),
                      "counters": attn_counters(w, select, attn_mode(ws_attn))},
         "kernels_ms": {"attn_partition_states": {"mean": attn_ms, "median": med(t_attn)},
+                       "compose": {"mean": mean(t_compose), "median": med(t_compose)},
                        "merge_states": {"mean": merge_ms, "median": med(t_merge)},
                        "contrib": {"mean": mean(t_contrib), "median": med(t_contrib)}},
         "merge_roofline": {"bound": "hbm", "achieved": merge_gbs, "peak": PEAK_HBM_GBS, "unit": "GB/s",
