@@ -190,11 +190,12 @@ __device__ void weights_block(const MergeArgs& a) {
 // indices in 32-bit arithmetic (a 64-bit division by a run-time value is a
 // long instruction sequence in front of the LSE loads).
 // W: with weight workgroups, in instances of their own: a composition without
-// weights keeps its registers and waves (bf16 states, 4 / 8 / 16 / 64 slots:
-// 35 / 55 / 65 / 142 registers; 60 / 100 / 101 / 196 while it carried the
-// weights' code.  3,000 rows x 12 heads x 20 slots at D=128 43.4 -> 36.9 us,
-// 4,095 x 12 x 5 14.9 -> 13.4; 9,450 x 40 x 8 138.0 -> 139.0: a launch that
-// HBM bounds alone gains nothing from more waves).
+// weights keeps its registers and waves (bf16 states, D=128, 4 / 8 / 16 / 64
+// slots: 38 / 58 / 68 / 142 registers, with weights 36 / 57 / 79 / 195; one
+// instance for both, with the final sums in it, took 60 / 100 / 101 / 196.
+// 3,000 rows x 12 heads x 20 slots 43.4 -> 36.9 us, 4,095 x 12 x 5 14.9 ->
+// 13.4; 9,450 x 40 x 8 138.0 -> 139.0: a launch that HBM alone bounds gains
+// nothing from more waves).
 template <typename TS, typename TO, int D, int NMAX, bool IDX32, bool W>
 __global__ __launch_bounds__(kMergeThreads) void merge_kernel(const MergeArgs a) {
   constexpr int CPR = D / 8;                      // chunks (lanes) per row
@@ -332,7 +333,11 @@ hipError_t launch_merge_d(const MergeArgs& a, int D, hipStream_t s) {
 // that order (each lane writing its own row put the 64 lanes of a store 4 * P
 // bytes apart).  24 heads x 8,192 rows x 16 partitions, both kernels: 31.0 ->
 // 15.8 us with the rows (26 MB), 18.1 -> 13.1 us without: the final sums take
-// one workgroup per partition instead of one for all.
+// one workgroup per partition instead of one for all.  The weights stay in
+// registers until they are staged: 207 of them in the 64-partition instance
+// (145 when each lane wrote its row), two waves per SIMD instead of three,
+// and still faster (3,000 rows x 12 heads x 40: 45.3 -> 31.1 us with the rows,
+// 40.2 -> 23.1 without).
 constexpr int kRowsStage = 16;
 
 template <int PMAX>

@@ -59,7 +59,9 @@ def compose_pairs(groups: Sequence[Tuple[int, int]], q: int, k: int = 2) -> List
 
 
 class GroupedSelectiveAttention:
-    """Selective attention with group-granular state reuse for one query block."""
+    """Selective attention with group-granular state reuse for one query block.
+    The steps of one instance share its states and workspaces: order them on one
+    stream, or across streams by events."""
 
     def __init__(self, B: int, H: int, D: int, offsets: Sequence[int], q: int, g: int, scale: float,
                  dtype: torch.dtype = torch.bfloat16, device="cuda",

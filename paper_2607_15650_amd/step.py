@@ -4,7 +4,7 @@ Each query block owns a state cache (one OUT slot and one LSE slot per key /
 value partition) that persists across steps: the paper's attention-state
 cache (Sec. 5.2).  A step computes the selected partitions fresh into their
 slots (the others keep the state of the step at which they were last
-computed), composes all slots, and measures the contribution weights.  All
+computed), then composes all slots and measures the contribution weights.  All
 work runs in the HIP kernels behind the C ABI; this module only owns buffers
 and calls them in order on the current stream.
 """
@@ -34,6 +34,9 @@ class SelectiveAttention:
     partition i of the same sequence.  ``state_dtype`` is the dtype of the
     cached states: the input dtype (default) or float32 for bf16 inputs; the
     composed output is in the input dtype either way.
+
+    The steps of one instance share its workspaces, whatever the query block:
+    order them on one stream, or across streams by events.
     """
 
     def __init__(self, B: int, H: int, D: int, offsets: Sequence[int], scale: float,
