@@ -29,6 +29,7 @@ def api():
 CASES = [
     (128, 8, [3000, 200, 1500, 64, 0], (0, 1, 2, 3), 40),
     (64, 8, [2500, 900, 33], (0, 2), 60),
+    (128, 4, [700], (0,), 17),            # few equal tasks: none is claimed, the counters are left alone
     (128, 3, [700, 300], (0, 1), 17),     # 102 tasks, less than a round: the six past the lists' common length
 ]
 
@@ -64,8 +65,9 @@ def test_balanced_launch_equals_static(D, H, lens, select, q_tiles):
     for rep, fill in enumerate((0x00, 0x7F, 0xFF, 0x01, 0x7F)):
         queue.fill_(fill)                   # stale counters: the launch resets them
         s_bal, l_bal = launch(queue)
-        # tasks were claimed: the counters were reset and counted up
-        assert not torch.equal(queue[:64], torch.full_like(queue[:64], fill)), (rep, fill)
+        # where tasks are claimed, the counters were reset and counted up
+        left_alone = torch.equal(queue[:64], torch.full_like(queue[:64], fill))
+        assert left_alone == (len(select) == 1), (rep, fill)
         assert torch.equal(s_bal.view(torch.uint8), s_static.view(torch.uint8)), (rep, fill)
         assert torch.equal(l_bal.view(torch.int32), l_static.view(torch.int32)), (rep, fill)
     for j in range(P):
